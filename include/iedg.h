@@ -139,7 +139,8 @@ iedg_status iedg_mesh_query(iedg_mesh mesh, iedg_mesh_info* info, int32_t* order
  *   U on and above) is stored in row perm[i] of LU, and likewise row i of
  *   U12 and entry i of w sit in row perm[i] (the row of A they came from).
  *   L21, Ke and r are indexed by the rows of C.
- * Outputs must not overlap inputs.  A zero or non-finite pivot latches
+ * Outputs must not overlap inputs or each other (Ke holds intermediate values
+ * until the Schur complement is written).  A zero or non-finite pivot latches
  * IEDG_ERR_SINGULAR with the element index.
  * Limits: n a multiple of 4 and at most 2560, t even and at most 1024
  * (IEDG_ERR_UNSUPPORTED otherwise); every array 16-byte aligned, as device
@@ -162,17 +163,16 @@ iedg_status iedg_condense_rhs(iedg_context ctx, int32_t n_elem, int32_t n_local,
                               hipStream_t stream);
 
 /* Batched condensation (section 2.2.1, eq. LS) of several meshes (segments)
- * in one persistent launch: one workgroup per CU slot takes (segment,
- * element) items from a device queue until it is empty.  Each item is
- * computed exactly as iedg_condense computes it (bitwise the same outputs,
- * with the sub-panel width the context held for that size when the plan was
- * made).  Segments may differ in element size (iedg_batch_create_sized:
+ * together: the elements of every segment of one size go through one launch
+ * sequence.  Each is computed exactly as iedg_condense computes it (bitwise
+ * the same outputs, with the sub-panel and panel widths the context held for
+ * that size when the plan was made).  Segments may differ in element size (iedg_batch_create_sized:
  * n_local[s], n_trace_elem[s] per segment, each a size iedg_condense
- * accepts); the work list starts with the largest elements and interleaves
- * the segments of one size.  The plan copies the segment table and work list
- * to the device once; iedg_condense_batched only launches (a reset kernel
- * and the condensation; it can be captured in a HIP graph).  Calls with one
- * plan must not overlap (they share the queue counter).  Segment pointers
+ * accepts); the sequences run from the largest elements down, each
+ * interleaving its segments.  The plan copies the segment table and work list
+ * to the device once; iedg_condense_batched only launches (it can be captured
+ * in a HIP graph).  Calls with one plan must not overlap (they write the same
+ * outputs).  Segment pointers
  * must stay valid for the plan's lifetime.  iedg_batch_create is the
  * one-size form.  Errors: IEDG_ERR_INVALID_ARG (sizes, null or unaligned
  * arrays of a segment with elements), IEDG_ERR_UNSUPPORTED (size or

@@ -170,8 +170,8 @@ def alloc_condense_out(E, n, t, prec, device, with_rhs=True):
 
 
 class CondenseBatch:
-    """Plan for one persistent condensation launch over several segments
-    (meshes), of one element size or of several (iedg_batch_create_sized).
+    """Plan for condensing several segments (meshes) together, of one element
+    size or of several, one launch sequence a size (iedg_batch_create_sized).
     `segments` is a list of (inputs, outputs) dicts: inputs A, B, C, D, F (F
     may be None), outputs as from alloc_condense_out.  Tensors must outlive
     the plan."""

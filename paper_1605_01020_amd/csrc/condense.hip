@@ -1,7 +1,7 @@
 // Element static condensation (section 2.2.1, eq. LS): host entry points,
 // the batched plan, the sub-panel width table and the right-hand-side
-// condensation kernel.  The condensation kernel itself is in
-// condense_kernel.h, compiled once per precision.
+// condensation kernel.  The condensation kernels themselves are in
+// condense_gemm.h, compiled once per precision, and condense_panel.hip.
 #include <initializer_list>
 
 #include "common.h"
@@ -97,14 +97,14 @@ static int tuned(iedg_context ctx, iedg_prec prec, int n, int iedg_context_s::Le
   }
   return fallback;
 }
-static int leaf_width(iedg_context ctx, iedg_prec prec, int n) {
-  return tuned(ctx, prec, n, &iedg_context_s::LeafChoice::lw, true);
-}
-// The panel width is not taken over from FP32: BF16 operands favour other
-// widths (the operands are rounded on every fragment read).
-static int panel_width(iedg_context ctx, iedg_prec prec, int n) {
-  const int ct = tuned(ctx, prec, n, &iedg_context_s::LeafChoice::ct, false);
-  return prec == IEDG_F64 ? 64 : ct;  // FP64 storage is built for 64 only
+// Sub-panel and panel width for elements of n local and t trace dofs.  The
+// panel width is not taken over from FP32: BF16 operands favour other widths.
+static void widths(iedg_context ctx, iedg_prec prec, int n, int t, int* lw, int* ct) {
+  const size_t es = prec == IEDG_F64 ? 8 : 4;
+  *lw = tuned(ctx, prec, n, &iedg_context_s::LeafChoice::lw, true);
+  *ct = prec == IEDG_F64 ? 64 : tuned(ctx, prec, n, &iedg_context_s::LeafChoice::ct, false);  // FP64 is built for 64
+  if (*lw == 0) *lw = default_leaf_width(es, n, t);
+  if (*ct == 0) *ct = default_panel_width(es, n);
 }
 
 }  // namespace iedg
@@ -139,19 +139,23 @@ extern "C" iedg_status iedg_condense(iedg_context ctx, int32_t n_elem, int32_t n
     return set_error(ctx, IEDG_ERR_UNSUPPORTED, "condense: n=%d t=%d too large", n_local, n_trace_elem);
   if (!aligned16({A, B, C, D, F, LU, perm, U12, L21, w, Ke, r}))
     return set_error(ctx, IEDG_ERR_INVALID_ARG, "condense: arrays must be 16-byte aligned");
+  if (prec != IEDG_F64 && prec != IEDG_F32 && prec != IEDG_BF16)
+    return set_error(ctx, IEDG_ERR_UNSUPPORTED, "condense: precision %d not built", (int)prec);
+  int lw, ct;
+  widths(ctx, prec, n_local, n_trace_elem, &lw, &ct);
   hipError_t err;
   if (prec == IEDG_F64) {
-    CondenseArgs<double> a{n_elem, n_local, n_trace_elem, A, B, C, D, F,
-                           (double*)LU, (double*)U12, (double*)L21, (double*)Ke, perm, w, r, ctx->d_status, 0};
-    err = condense_launch_f64(a, nullptr, QueueLaunch{}, leaf_width(ctx, prec, n_local), 64, stream);
-  } else if (prec == IEDG_F32 || prec == IEDG_BF16) {
-    CondenseArgs<float> a{n_elem, n_local, n_trace_elem, A, B, C, D, F,
-                          (float*)LU, (float*)U12, (float*)L21, (float*)Ke, perm, w, r, ctx->d_status, 0};
-    const int lw = leaf_width(ctx, prec, n_local), ct = panel_width(ctx, prec, n_local);
-    err = prec == IEDG_F32 ? condense_launch_f32(a, nullptr, QueueLaunch{}, lw, ct, stream)
-                           : condense_launch_bf16(a, nullptr, QueueLaunch{}, lw, ct, stream);
+    CondenseWork<double> wk{};
+    wk.a = {n_elem, n_local, n_trace_elem, A, B, C, D, F, (double*)LU, (double*)U12, (double*)L21, (double*)Ke, perm, w, r,
+            ctx->d_status};
+    wk.count = n_elem; wk.n = n_local; wk.t = n_trace_elem;
+    err = condense_run_f64(wk, lw, ct, stream);
   } else {
-    return set_error(ctx, IEDG_ERR_UNSUPPORTED, "condense: precision %d not built", (int)prec);
+    CondenseWork<float> wk{};
+    wk.a = {n_elem, n_local, n_trace_elem, A, B, C, D, F, (float*)LU, (float*)U12, (float*)L21, (float*)Ke, perm, w, r,
+            ctx->d_status};
+    wk.count = n_elem; wk.n = n_local; wk.t = n_trace_elem;
+    err = prec == IEDG_F32 ? condense_run_f32(wk, lw, ct, stream) : condense_run_bf16(wk, lw, ct, stream);
   }
   if (err != hipSuccess) return hip_check(ctx, err, "condense launch");
   return IEDG_OK;
@@ -188,11 +192,11 @@ extern "C" iedg_status iedg_condense_rhs(iedg_context ctx, int32_t n_elem, int32
 // ---- batched condensation ---------------------------------------------------
 struct iedg_batch_s {
   iedg_context ctx = nullptr;
-  int n_max = 0, n_items = 0, n_wg = 0;
   iedg_prec prec = IEDG_F64;
   void* d_segs = nullptr;   // CondenseArgs<T>[n_seg]
-  int2* d_items = nullptr;  // (segment, element) work list
-  int* d_counter = nullptr; // queue position of the persistent launch
+  int2* d_items = nullptr;  // (segment, element) work list, one run per size class
+  struct Class { int first, count, n, t, lw, ct; };
+  std::vector<Class> classes;
 };
 
 extern "C" iedg_status iedg_batch_create_sized(iedg_context ctx, int32_t n_seg, const iedg_condense_segment* segs,
@@ -205,7 +209,6 @@ extern "C" iedg_status iedg_batch_create_sized(iedg_context ctx, int32_t n_seg, 
   *out = nullptr;
   std::vector<CondenseArgs<double>> a64;
   std::vector<CondenseArgs<float>> a32;
-  int n_max = 0;
   for (int s = 0; s < n_seg; ++s) {
     const iedg_condense_segment& g = segs[s];
     const int n = n_local[s], t = n_trace_elem[s];
@@ -217,56 +220,44 @@ extern "C" iedg_status iedg_batch_create_sized(iedg_context ctx, int32_t n_seg, 
     if (g.F && (!g.w || !g.r)) return set_error(ctx, IEDG_ERR_INVALID_ARG, "batch_create: segment %d F without w, r", s);
     if (!aligned16({g.A, g.B, g.C, g.D, g.F, g.LU, g.perm, g.U12, g.L21, g.w, g.Ke, g.r}))
       return set_error(ctx, IEDG_ERR_INVALID_ARG, "batch_create: segment %d arrays must be 16-byte aligned", s);
-    // the width iedg_condense would use for this size now (context table or default)
-    int lw = leaf_width(ctx, prec, n), ct = panel_width(ctx, prec, n);
-    if (lw == 0) lw = default_leaf_width(prec == IEDG_F64 ? 8 : 4, n, t);
-    if (ct == 0) ct = default_panel_width(prec == IEDG_F64 ? 8 : 4, n);
-    if (g.n_elem > 0) n_max = std::max(n_max, n);
     a64.push_back(CondenseArgs<double>{g.n_elem, n, t, g.A, g.B, g.C, g.D, g.F, (double*)g.LU, (double*)g.U12,
-                                       (double*)g.L21, (double*)g.Ke, g.perm, g.w, g.r, ctx->d_status, lw, ct});
+                                       (double*)g.L21, (double*)g.Ke, g.perm, g.w, g.r, ctx->d_status});
     a32.push_back(CondenseArgs<float>{g.n_elem, n, t, g.A, g.B, g.C, g.D, g.F, (float*)g.LU, (float*)g.U12,
-                                      (float*)g.L21, (float*)g.Ke, g.perm, g.w, g.r, ctx->d_status, lw, ct});
+                                      (float*)g.L21, (float*)g.Ke, g.perm, g.w, g.r, ctx->d_status});
   }
-  // Work list: size classes from the largest element down (the long items
-  // start first, the persistent workgroups finish on short ones); within a
-  // class the segments interleave, so that concurrently running workgroups
-  // read different meshes' memory.
+  // Work list: size classes from the largest element down, each one launch
+  // sequence; within a class the segments interleave, so that concurrently
+  // running workgroups read different meshes' memory.
   std::vector<int> seg_order(n_seg);
   for (int s = 0; s < n_seg; ++s) seg_order[s] = s;
   std::stable_sort(seg_order.begin(), seg_order.end(), [&](int x, int y) {
     return n_local[x] != n_local[y] ? n_local[x] > n_local[y] : n_trace_elem[x] > n_trace_elem[y];
   });
   std::vector<int2> items;
+  std::vector<iedg_batch_s::Class> classes;
   for (size_t c0 = 0; c0 < seg_order.size();) {
     size_t c1 = c0;
     int maxE = 0;
     while (c1 < seg_order.size() && n_local[seg_order[c1]] == n_local[seg_order[c0]] &&
            n_trace_elem[seg_order[c1]] == n_trace_elem[seg_order[c0]])
       maxE = std::max(maxE, (int)segs[seg_order[c1++]].n_elem);
+    // the widths iedg_condense would use for this size now (context table or default)
+    iedg_batch_s::Class c{(int)items.size(), 0, n_local[seg_order[c0]], n_trace_elem[seg_order[c0]], 0, 0};
+    widths(ctx, prec, c.n, c.t, &c.lw, &c.ct);
     for (int e = 0; e < maxE; ++e)
       for (size_t k = c0; k < c1; ++k)
         if (e < segs[seg_order[k]].n_elem) items.push_back(make_int2(seg_order[k], e));
+    c.count = (int)items.size() - c.first;
+    if (c.count) classes.push_back(c);
     c0 = c1;
   }
   auto* b = new iedg_batch_s();
   b->ctx = ctx;
-  b->n_max = n_max;
   b->prec = prec;
-  b->n_items = (int)items.size();
-  if (!items.empty()) {
-    const int slots = prec == IEDG_F64   ? condense_queue_slots_f64(n_max)
-                      : prec == IEDG_F32 ? condense_queue_slots_f32(n_max)
-                                         : condense_queue_slots_bf16(n_max);
-    if (slots <= 0) {
-      delete b;
-      return set_error(ctx, IEDG_ERR_HIP, "batch_create: no occupancy for n=%d", n_max);
-    }
-    b->n_wg = std::min(slots, b->n_items);
-  }
+  b->classes = std::move(classes);
   const size_t seg_bytes = prec == IEDG_F64 ? a64.size() * sizeof(a64[0]) : a32.size() * sizeof(a32[0]);
   hipError_t e = hipMalloc(&b->d_segs, seg_bytes);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&b->d_items), std::max<size_t>(1, items.size()) * sizeof(int2));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&b->d_counter), sizeof(int));
   if (e == hipSuccess)
     e = hipMemcpy(b->d_segs, prec == IEDG_F64 ? (const void*)a64.data() : (const void*)a32.data(), seg_bytes,
                   hipMemcpyHostToDevice);
@@ -289,15 +280,23 @@ extern "C" iedg_status iedg_batch_create(iedg_context ctx, int32_t n_seg, const 
 
 extern "C" iedg_status iedg_condense_batched(iedg_context ctx, iedg_batch b, hipStream_t stream) {
   if (!ctx || !b) return IEDG_ERR_INVALID_ARG;
-  if (b->n_items == 0) return IEDG_OK;
-  const QueueLaunch q{b->d_items, b->n_items, b->n_max, b->n_wg, b->d_counter};
-  hipError_t err;
-  if (b->prec == IEDG_F64)
-    err = condense_launch_f64(CondenseArgs<double>{}, (const CondenseArgs<double>*)b->d_segs, q, 0, 0, stream);
-  else if (b->prec == IEDG_BF16)
-    err = condense_launch_bf16(CondenseArgs<float>{}, (const CondenseArgs<float>*)b->d_segs, q, 0, 0, stream);
-  else
-    err = condense_launch_f32(CondenseArgs<float>{}, (const CondenseArgs<float>*)b->d_segs, q, 0, 0, stream);
+  hipError_t err = hipSuccess;
+  for (const auto& c : b->classes) {
+    if (err != hipSuccess) break;
+    if (b->prec == IEDG_F64) {
+      CondenseWork<double> wk{};
+      wk.segs = (const CondenseArgs<double>*)b->d_segs;
+      wk.items = b->d_items + c.first;
+      wk.count = c.count; wk.n = c.n; wk.t = c.t;
+      err = condense_run_f64(wk, c.lw, c.ct, stream);
+    } else {
+      CondenseWork<float> wk{};
+      wk.segs = (const CondenseArgs<float>*)b->d_segs;
+      wk.items = b->d_items + c.first;
+      wk.count = c.count; wk.n = c.n; wk.t = c.t;
+      err = b->prec == IEDG_F32 ? condense_run_f32(wk, c.lw, c.ct, stream) : condense_run_bf16(wk, c.lw, c.ct, stream);
+    }
+  }
   if (err != hipSuccess) return hip_check(ctx, err, "condense_batched launch");
   return IEDG_OK;
 }
@@ -306,7 +305,6 @@ extern "C" void iedg_batch_destroy(iedg_batch b) {
   if (!b) return;
   if (b->d_segs) hipFree(b->d_segs);
   if (b->d_items) hipFree(b->d_items);
-  if (b->d_counter) hipFree(b->d_counter);
   delete b;
 }
 

@@ -1,0 +1,100 @@
+"""GPU parity of the condensation at the edges of its tiles: sizes around the
+panel (64, 128), sub-panel (8, 16) and tile (128) widths, and trace blocks too
+small to hold a panel's inverse (t < 64 or, with two panel halves, t < 111:
+the inverse is then formed again by the panel-row kernel).
+
+Tolerances: FP64 as for the element parity tests (K_e, r_e <= 1e-12, factor
+identities <= 1e-13); FP32 n^(1/2) 2^-24 times a growth of 64 stays below
+2e-4 at n = 1300; BF16 operands 2^-6 of the product, as rounding an operand
+costs at most 2^-9 relative and the factors grow it by less than 4."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import rel
+
+pytestmark = pytest.mark.gpu
+
+api = pytest.importorskip("paper_1605_01020_amd.api")
+from paper_1605_01020_amd import F64, F32, BF16  # noqa: E402
+
+SIZES = [(4, 2), (20, 30), (64, 64), (68, 130), (132, 128), (140, 6), (196, 112), (512, 120), (516, 256), (1300, 110)]
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    c = api.Context()
+    yield c
+    torch.cuda.synchronize()
+
+
+def _inputs(n, t, E=2):
+    g = torch.Generator().manual_seed(1000 * n + t)
+    def r(*s):
+        return torch.randn(*s, dtype=torch.float64, generator=g)
+    return dict(A=r(E, n, n) / n ** 0.5 + 2 * torch.eye(n, dtype=torch.float64), B=r(E, n, t) / n ** 0.5,
+                C=r(E, t, n) / n ** 0.5, D=r(E, t, t) / t ** 0.5 + 1.5 * torch.eye(t, dtype=torch.float64), F=r(E, n))
+
+
+@pytest.mark.parametrize("n,t", SIZES)
+def test_condense_edge_sizes(ctx, n, t):
+    h = _inputs(n, t)
+    d = {k: v.cuda() for k, v in h.items()}
+    for prec, widths in ((F64, [(8, 64), (16, 64)]), (F32, [(8, 64), (16, 64), (8, 128), (16, 128)]),
+                         (BF16, [(16, 64), (16, 128)])):
+        for lw, ct in widths:
+            api.set_leaf_width(ctx, n, lw, prec=prec)
+            api.set_panel_width(ctx, n, ct, prec=prec)
+            print(f"[gpu-test] condense n={n} t={t} prec={int(prec)} widths {lw}/{ct}", flush=True)
+            o = {k: v.cpu().numpy().astype(np.float64) for k, v in
+                 api.condense(ctx, d["A"], d["B"], d["C"], d["D"], d["F"], prec=prec).items()}
+            ctx.sync_status()
+            for e in range(2):
+                A, B, C, D, F = (h[k][e].numpy() for k in "ABCDF")
+                Ke, re, _ = oracle.condense_element(A, B, C, D, F)
+                p = o["perm"][e].astype(np.int64)
+                assert sorted(p.tolist()) == list(range(n))
+                L = np.tril(o["LU"][e][p], -1) + np.eye(n)
+                U = np.triu(o["LU"][e][p])
+                tol = 1e-12 if prec == F64 else 2e-4 if prec == F32 else 2.0 ** -6
+                ident = 1e-13 if prec == F64 else tol
+                scale = np.linalg.norm(C @ np.linalg.solve(A, B))
+                assert np.linalg.norm(o["Ke"][e] - Ke) <= tol * (scale + np.linalg.norm(D))
+                assert rel(o["r"][e], re) <= tol
+                assert rel(L @ U, A[p]) <= ident
+                assert rel(L @ o["U12"][e][p], B[p]) <= ident
+                assert rel(L @ o["w"][e][p], F[p]) <= ident
+                assert rel(o["L21"][e] @ U, C) <= ident
+
+
+def test_condense_many_and_few_elements_agree(ctx):
+    """Few elements spread their tiles over the XCDs, many keep them on one:
+    the same element gives the same bits in both."""
+    n, t, E = 68, 66, 67
+    h = _inputs(n, t, E)
+    d = {k: v.cuda() for k, v in h.items()}
+    for prec in (F64, F32, BF16):
+        many = api.condense(ctx, d["A"], d["B"], d["C"], d["D"], d["F"], prec=prec)
+        few = api.condense(ctx, *(d[k][64:].contiguous() for k in "ABCDF"), prec=prec)
+        ctx.sync_status()
+        for k in many:
+            assert torch.equal(many[k][64:], few[k]), k
+
+
+def test_condense_singular_latched_once_per_column(ctx):
+    """A zero column leaves no pivot: the element is reported, the others are
+    not disturbed."""
+    n, t = 132, 130
+    h = _inputs(n, t, 3)
+    h["A"][1, :, 70] = 0.0
+    d = {k: v.cuda() for k, v in h.items()}
+    for prec in (F64, F32):
+        o = api.condense(ctx, d["A"], d["B"], d["C"], d["D"], d["F"], prec=prec)
+        with pytest.raises(Exception, match="singular"):
+            ctx.sync_status()
+        for e in (0, 2):
+            Ke, _, _ = oracle.condense_element(*(h[k][e].numpy() for k in "ABCDF"))
+            assert rel(o["Ke"][e].cpu().numpy(), Ke) <= (1e-12 if prec == F64 else 2e-4)
