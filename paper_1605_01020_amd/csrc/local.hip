@@ -86,61 +86,84 @@ __global__ __launch_bounds__(LTHR) void backsolve_kernel(int n, int t, int b, in
   for (int i = tid; i < n; i += LTHR) z[(size_t)e * n + i] = y[i];
 }
 
-// Per element: rF_e = F_e - A_e z_e - B_e u_e; q_e = C_e z_e + D_e u_e; also
-// per-element sums of rF^2 and F^2 (fixed-order block reduction).
-__global__ __launch_bounds__(LTHR) void residual_elem_kernel(int n, int t, int b, int S, const int32_t* elem_faces,
-                                                             const double* A, const double* B, const double* C,
-                                                             const double* D, const double* F, const double* z,
-                                                             const double* uhat, double* rF, double* q,
-                                                             double* part_rf, double* part_f) {
+// Rows of rF_e = F_e - A_e z_e - B_e u_e and of q_e = C_e z_e + D_e u_e: a
+// workgroup takes `rows` consecutive rows of an element's [A B; C D], a wave
+// four at a time with 16 loads in flight a lane.  Bound by HBM (every block is
+// read once).  Split by rows, because one workgroup an element leaves CUs idle
+// below 256 elements and in the last round above: 216 elements of n = 2500,
+// t = 750 took 5.87 ms (3.1 TB/s) so, 3.00 ms (6.1 TB/s) split.  The element's
+// first workgroup also sums F^2, before any row of it is written.
+constexpr int RROWS = 64;
+
+__global__ __launch_bounds__(LTHR) void residual_elem_kernel(int n, int t, int b, int S, int rows, int chunks,
+                                                             const int32_t* elem_faces, const double* A,
+                                                             const double* B, const double* C, const double* D,
+                                                             const double* F, const double* z, const double* uhat,
+                                                             double* rF, double* q, double* part_f) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* ue = reinterpret_cast<double*>(smem_raw);  // t
   double* ze = ue + t;                               // n
   double* red = ze + n;                              // LWAVES
-  double* acc = red + LWAVES;                        // 2 * LWAVES
-  const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int e = blockIdx.x / chunks, r0 = (blockIdx.x % chunks) * rows;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   for (int i = tid; i < t; i += LTHR) {
     const int a = i / b, l = i % b;
     ue[i] = uhat[(size_t)elem_faces[S * e + a] * b + l];
   }
   for (int i = tid; i < n; i += LTHR) ze[i] = z[(size_t)e * n + i];
+  if (r0 == 0) {
+    double f2 = 0.0;
+    for (int i = tid; i < n; i += LTHR) f2 += F[(size_t)e * n + i] * F[(size_t)e * n + i];
+    f2 = block_sum(f2, red);
+    if (tid == 0) part_f[e] = f2;
+  }
   __syncthreads();
   const size_t nn = (size_t)n * n, nt = (size_t)n * t, tt = (size_t)t * t;
   const double *Ae = A + e * nn, *Be = B + e * nt, *Ce = C + e * nt, *De = D + e * tt;
-  double srf = 0.0, sf = 0.0;  // per-wave partials (lane 0)
-  for (int i = wv; i < n; i += LWAVES) {
-    const double s = wave_dot<double>(Ae + (size_t)i * n, ze, n) + wave_dot<double>(Be + (size_t)i * t, ue, t);
-    if (lane == 0) {
-      const double f = F[(size_t)e * n + i];
-      const double v = f - s;
-      rF[(size_t)e * n + i] = v;
-      srf += v * v;
-      sf += f * f;
+  const int r1 = min(r0 + rows, n + t);
+  for (int i = r0 + 4 * wv; i < r1; i += 4 * LWAVES) {
+    const double *left[4], *right[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = min(i + r, r1 - 1);
+      left[r] = row < n ? Ae + (size_t)row * n : Ce + (size_t)(row - n) * n;
+      right[r] = row < n ? Be + (size_t)row * t : De + (size_t)(row - n) * t;
     }
-  }
-  for (int i = wv; i < t; i += LWAVES) {
-    const double s = wave_dot<double>(Ce + (size_t)i * n, ze, n) + wave_dot<double>(De + (size_t)i * t, ue, t);
-    if (lane == 0) q[(size_t)e * t + i] = s;
-  }
-  if (lane == 0) { acc[2 * wv] = srf; acc[2 * wv + 1] = sf; }
-  __syncthreads();
-  if (tid == 0) {
-    double a0 = 0.0, a1 = 0.0;
-    for (int k = 0; k < LWAVES; ++k) { a0 += acc[2 * k]; a1 += acc[2 * k + 1]; }
-    part_rf[e] = a0;
-    part_f[e] = a1;
+    double s[4], s2[4];
+    wave_dot_rows<double, 4>(left, ze, n, s);
+    wave_dot_rows<double, 4>(right, ue, t, s2);
+    if (lane < 4 && i + lane < r1) {
+      double v = s[0] + s2[0];
+#pragma unroll
+      for (int r = 1; r < 4; ++r) v = lane == r ? s[r] + s2[r] : v;
+      const int row = i + lane;
+      if (row < n) rF[(size_t)e * n + row] = F[(size_t)e * n + row] - v;
+      else q[(size_t)e * t + row - n] = v;
+    }
   }
 }
 
 // rG = G - sum_e P_e^T q_e (list order: ascending e, a) and per-unit sums of
-// rG^2, G^2 (b <= 128 dofs a unit, one workgroup of 128 threads a unit).
-__global__ __launch_bounds__(128) void residual_face_kernel(int b, int t, int S, const int32_t* src_ptr,
+// rG^2, G^2 (b <= 128 dofs a unit, one workgroup of 128 threads a unit); the
+// workgroups past the units sum rF^2 of one element each.  Every sum
+// has a fixed order.
+__global__ __launch_bounds__(128) void residual_face_kernel(int NF, int n, int b, int t, int S, const int32_t* src_ptr,
                                                             const int32_t* src_list, const double* q,
-                                                            const double* G, double* rG, double* part_rg,
-                                                            double* part_g) {
+                                                            const double* G, const double* rF, double* rG,
+                                                            double* part_rg, double* part_g, double* part_rf) {
   __shared__ double red[2];
   const int f = blockIdx.x, l = threadIdx.x;
   double v = 0.0, g = 0.0;
+  if (f >= NF) {
+    const int e = f - NF;
+    const double* re = rF + (size_t)e * n;
+    for (int i = l; i < n; i += 128) v += re[i] * re[i];
+    v = wave_sum(v);
+    if (l == 64) red[0] = v;
+    __syncthreads();
+    if (l == 0) part_rf[e] = v + red[0];
+    return;
+  }
   if (l < b) {
     const size_t i = (size_t)f * b + l;
     g = G[i];
@@ -216,13 +239,19 @@ static iedg_status residual_launch(iedg_context ctx, iedg_mesh mesh, int n, cons
   double* pf = prf + E;
   double* prg = pf + E;
   double* pg = prg + NF;
-  const size_t smem = sizeof(double) * (t + n + 3 * LWAVES);
+  const size_t smem = sizeof(double) * (t + n + LWAVES);
+  // rF written over F or z: the whole element in one workgroup, which reads
+  // both before it writes
+  const double* last = rF + (size_t)E * n;
+  const bool over = (F < last && rF < F + (size_t)E * n) || (z < last && rF < z + (size_t)E * n);
+  const int rows = over ? n + t : RROWS, chunks = (n + t + rows - 1) / rows;
+  if ((int64_t)E * chunks > INT32_MAX) return set_error(ctx, IEDG_ERR_UNSUPPORTED, "residual: %d elements of n=%d", E, n);
   IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(residual_elem_kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  hipLaunchKernelGGL(residual_elem_kernel, dim3(E), dim3(LTHR), smem, stream, n, t, b, mesh->slots, mesh->d_elem_faces, A, B, C, D,
-                     F, z, uhat, rF, q, prf, pf);
-  hipLaunchKernelGGL(residual_face_kernel, dim3(NF), dim3(128), 0, stream, b, t, mesh->slots, mesh->d_src_ptr,
-                     mesh->d_src_list, q, G, rG, prg, pg);
+  hipLaunchKernelGGL(residual_elem_kernel, dim3(E * chunks), dim3(LTHR), smem, stream, n, t, b, mesh->slots, rows, chunks,
+                     mesh->d_elem_faces, A, B, C, D, F, z, uhat, rF, q, pf);
+  hipLaunchKernelGGL(residual_face_kernel, dim3(NF + E), dim3(128), 0, stream, NF, n, b, t, mesh->slots, mesh->d_src_ptr,
+                     mesh->d_src_list, q, G, rF, rG, prg, pg, prf);
   hipLaunchKernelGGL(sum4_kernel, dim3(4), dim3(64), 0, stream, prf, (int64_t)E, prg, (int64_t)NF, pf, (int64_t)E, pg,
                      (int64_t)NF, sums);
   IEDG_LAUNCH_CHECK(ctx, "residual launch");

@@ -98,3 +98,28 @@ def test_condense_singular_latched_once_per_column(ctx):
         for e in (0, 2):
             Ke, _, _ = oracle.condense_element(*(h[k][e].numpy() for k in "ABCDF"))
             assert rel(o["Ke"][e].cpu().numpy(), Ke) <= (1e-12 if prec == F64 else 2e-4)
+
+
+def test_residual_in_place(ctx):
+    """rF over F, and rF over z: each element's rows are read before any is
+    written; rows past the last full chunk of 64 included (n + t = 280)."""
+    from synth import StructuredHexMesh, ElementSpec
+    m, spec = StructuredHexMesh(2, 2, 1), ElementSpec(1)
+    mesh = api.Mesh(ctx, m.elem_faces(), m.n_face, spec.b)
+    h = _inputs(spec.n, spec.t, m.n_elem)
+    d = {k: v.cuda() for k, v in h.items()}
+    g = torch.Generator().manual_seed(9)
+    z = torch.randn(m.n_elem, spec.n, dtype=torch.float64, generator=g).cuda()
+    u = torch.randn(mesh.n_trace, dtype=torch.float64, generator=g).cuda()
+    G = torch.randn(mesh.n_trace, dtype=torch.float64, generator=g).cuda()
+    blk = [d[k] for k in "ABCD"]
+    rF, rG, s = api.residual_full(ctx, mesh, *blk, d["F"], G, z, u)
+    idx = torch.as_tensor(m.elem_faces()).long().cuda()[:, :, None] * spec.b + torch.arange(spec.b).cuda()
+    ue = u[idx.reshape(m.n_elem, -1)]
+    ref = d["F"] - torch.matmul(d["A"], z[:, :, None])[:, :, 0] - torch.matmul(d["B"], ue[:, :, None])[:, :, 0]
+    assert rel(rF.cpu().numpy(), ref.cpu().numpy()) <= 1e-14
+    assert abs(s[2].item() / d["F"].square().sum().item() - 1) <= 1e-14
+    for over in ("F", "z"):
+        f, zz = d["F"].clone(), z.clone()
+        r2, g2, s2 = api.residual_full(ctx, mesh, *blk, f, G, zz, u, rF=f if over == "F" else zz)
+        assert torch.equal(r2, rF) and torch.equal(g2, rG) and torch.equal(s2, s), over
