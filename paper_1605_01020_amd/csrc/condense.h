@@ -150,14 +150,17 @@ inline dim3 condense_grid(const CondenseWork<T>& wk, int tiles) {
 // triangle's rows kp .. kp+sw (Lb, LW x 64, strictly lower part):
 //   inv = [L11^{-1} 0; -L22^{-1} L21 L11^{-1}  L22^{-1}].
 // Every product is an ascending chain of fused multiply-adds (the MFMA sums
-// its four products in that order, measured against fma), zeros aside.  Y:
-// LW x 64 of LDS.  Called by every thread; ends with a barrier.
+// its four products in that order, measured against fma), zeros aside.  L22 is
+// inverted by one wave as a chain of rank-one MFMAs on the identity, each with
+// one nonzero k, while others form L21 L11^{-1}: in vector registers its rows
+// would cost more than the rest of the growth.  Y: LW x 64 of LDS.  Called by
+// every thread; ends with a barrier.
 template <typename T, int LW>
 __device__ __forceinline__ void grow_inverse(T* Li, int LS, const T* Lb, T* Y, int kp, int sw) {
   typedef Mfma<T> MF;
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
-  const int kb = (kp + 15) / 16;  // column blocks of the finished part
+  const int kb = (kp + 15) / 16;  // column blocks of the finished part (at most 3)
   for (int b = wv; b < kb; b += nw) {
     typename MF::acc_t acc = MF::zero();
     for (int m = 0; m < 16 * kb; m += 4) {
@@ -171,20 +174,26 @@ __device__ __forceinline__ void grow_inverse(T* Li, int LS, const T* Lb, T* Y, i
       if (row < LW) Y[row * 64 + 16 * b + li] = acc[v];
     }
   }
-  __syncthreads();
-  if (tid < sw) {  // L22^{-1} by columns
-    T v[LW];
+  if (wv == nw - 1) {
+    // L22^{-1}: row i takes -L[i][m] (row m) for m = 0 .. i-1 in turn
+    typename MF::acc_t acc;
+    T av[4];
 #pragma unroll
-    for (int i = 0; i < LW; ++i) {
-      T acc = i == tid ? T(1) : T(0);
-      asm volatile("" ::: "memory");  // (row by row: all of Lb at once would not fit the registers)
-#pragma unroll
-      for (int m = 0; m < i; ++m) acc = fma(-Lb[i * 64 + kp + m], v[m], acc);
-      v[i] = acc;
+    for (int v = 0; v < 4; ++v) {
+      const int m = MF::row(lane, v);  // this lane group's row in register v
+      acc[v] = m == li ? T(1) : T(0);
+      av[v] = (m < sw && li < sw && li > m) ? -Lb[li * 64 + kp + m] : T(0);
     }
 #pragma unroll
-    for (int i = 0; i < LW; ++i)
-      if (i < sw) Li[(kp + i) * LS + kp + tid] = v[i];
+    for (int m = 0; m < LW; ++m) {
+      const int v = sizeof(T) == 4 ? m & 3 : m >> 2, g = sizeof(T) == 4 ? m >> 2 : m & 3;  // MF::row(16 g, v) == m
+      acc = MF::mac(lg == g ? av[v] : T(0), lg == g ? acc[v] : T(0), acc);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = MF::row(lane, v);
+      if (row < sw && li < sw) Li[(kp + row) * LS + kp + li] = acc[v];
+    }
   }
   __syncthreads();
   for (int b = wv; b < kb; b += nw) {

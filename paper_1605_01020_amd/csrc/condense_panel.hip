@@ -30,8 +30,8 @@
 
 namespace iedg {
 
-// Wave-wide maximum without a round trip through LDS: two quad permutations
-// and two rotations inside each 16-lane row (DPP) leave the row's extremum in
+// Maximum over 16-lane rows, and over the wave, without a round trip through
+// LDS: two quad permutations and two rotations (DPP) leave a row's maximum in
 // every lane of the row; the four rows are then read as uniform values.
 constexpr int kDppXor1 = 0xB1;   // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;   // quad_perm [2,3,0,1]
@@ -39,16 +39,18 @@ constexpr int kDppRor4 = 0x124;  // row_ror:4
 constexpr int kDppRor8 = 0x128;  // row_ror:8
 
 template <int CTRL>
-__device__ __forceinline__ int dpp_i32(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+__device__ __forceinline__ unsigned dpp_max(unsigned v) {
+  return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true));
 }
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v) {
-  return __int_as_float(dpp_i32<CTRL>(__float_as_int(v)));
+__device__ __forceinline__ unsigned row_max(unsigned v) {
+  return dpp_max<kDppRor8>(dpp_max<kDppRor4>(dpp_max<kDppXor2>(dpp_max<kDppXor1>(v))));
 }
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v) {
-  return __hiloint2double(dpp_i32<CTRL>(__double2hiint(v)), dpp_i32<CTRL>(__double2loint(v)));
+__device__ __forceinline__ unsigned read_lane(unsigned v, int l) {
+  return (unsigned)__builtin_amdgcn_readlane((int)v, l);
+}
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
+  v = row_max(v);
+  return max(max(read_lane(v, 0), read_lane(v, 16)), max(read_lane(v, 32), read_lane(v, 48)));
 }
 __device__ __forceinline__ int read_lane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
 __device__ __forceinline__ float read_lane(float v, int l) {
@@ -58,32 +60,44 @@ __device__ __forceinline__ double read_lane(double v, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                           __builtin_amdgcn_readlane(__double2loint(v), l));
 }
-// (values must not be NaN)
-template <typename T>
-__device__ __forceinline__ T row_max(T v) {
-  v = fmax(v, dpp_move<kDppXor1>(v));
-  v = fmax(v, dpp_move<kDppXor2>(v));
-  v = fmax(v, dpp_move<kDppRor4>(v));
-  return fmax(v, dpp_move<kDppRor8>(v));
-}
-template <typename T>
-__device__ __forceinline__ T wave_max(T v) {
-  v = row_max(v);
-  return fmax(fmax(read_lane(v, 0), read_lane(v, 16)), fmax(read_lane(v, 32), read_lane(v, 48)));
-}
 
-// The lane of `mask` (not empty) with the smallest value of pos.
-__device__ __forceinline__ int first_lane(unsigned long long mask, int pos) {
+// Magnitudes are compared by a 32-bit key, 0 where there is none: all of an
+// FP32 magnitude, the upper word of an FP64 one.
+__device__ __forceinline__ unsigned mag_key(float a) { return a < 0.f ? 0u : __float_as_uint(a) + 1u; }
+__device__ __forceinline__ unsigned mag_key(double a) { return a < 0.0 ? 0u : (unsigned)__double2hiint(a) + 1u; }
+
+// Of the lanes in `mask` (not empty) the one with the largest a, ties to the
+// smallest pos.  Mostly a single lane; FP64 lanes that share the key and equal
+// magnitudes take the loop.
+template <typename T>
+__device__ __forceinline__ int best_lane(unsigned long long mask, T a, int pos) {
   int best = __ffsll(mask) - 1;
   mask &= mask - 1;
-  if (mask) {  // several lanes hold the maximum
+  if (mask) {
+    T ba = read_lane(a, best);
     int bp = read_lane(pos, best);
     for (; mask; mask &= mask - 1) {
       const int l = __ffsll(mask) - 1, p = read_lane(pos, l);
-      if (p < bp) { bp = p; best = l; }
+      const T v = read_lane(a, l);
+      if (v > ba || (v == ba && p < bp)) { ba = v; bp = p; best = l; }
     }
   }
   return best;
+}
+
+// 4 x 4 transpose of 16-lane groups over four registers: register r of lane
+// group g takes what register g of lane group r held.
+__device__ __forceinline__ void swap32(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+__device__ __forceinline__ void swap16(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+__device__ __forceinline__ void transpose4(unsigned& a, unsigned& b, unsigned& c, unsigned& d) {
+  swap32(a, c); swap32(b, d);
+  swap16(a, b); swap16(c, d);
 }
 
 // A row of LW values in LDS is kept as four runs of LW / 4: entry j at
@@ -94,7 +108,7 @@ __device__ __forceinline__ constexpr int row_slot(int j) {
   return (j & 3) * (LW / 4) + (j >> 2);
 }
 
-template <typename T, int LW, int NT>
+template <typename T, int LW, int R, int NT>
 struct PanelSmem {
   static constexpr int NW = NT / 64, LIS = 65;
   T Li[64 * LIS];        // inverse of the panel's factored columns so far
@@ -106,12 +120,20 @@ struct PanelSmem {
   T cval[2][NW];         // the candidates' pivot entries
   int cidx[2][NW];       // and positions
   int prow[64];          // physical rows of the panel's pivots
+  T* rowp[NT * R];       // every row slot's row in LU or L21 (LU past the last)
+  int phys[NT * R];      // and its physical row (rows of A)
 };
 
-// A row's columns in registers, in quads (the rank-one update's accumulators).
+// A row's columns in registers, in quads (the FP32 rank-one update's
+// accumulators; FP64 values need no common registers).
+struct DoubleQuad {
+  double a[4];
+  __device__ __forceinline__ double& operator[](int i) { return a[i]; }
+  __device__ __forceinline__ const double& operator[](int i) const { return a[i]; }
+};
 template <typename T> struct Quad;
 template <> struct Quad<float> { typedef f4 v; };
-template <> struct Quad<double> { typedef d4 v; };
+template <> struct Quad<double> { typedef DoubleQuad v; };
 
 // x -= l u over a row's columns past KK (KK < 0: all), u in the lane's share
 // layout with the columns up to KK zero.
@@ -142,7 +164,7 @@ __device__ __forceinline__ void put_row(const Q4 (&x)[R][LW / 4], int q, int kk,
 // One pivot column KK of a sub-panel in registers: k is its pivot position,
 // pos[q] the position of slot q's row.
 template <typename T, int LW, int R, int NT, int KK>
-__device__ __forceinline__ void pivot_column(PanelSmem<T, LW, NT>& sm, typename Quad<T>::v (&x)[R][LW / 4], int (&pos)[R],
+__device__ __forceinline__ void pivot_column(PanelSmem<T, LW, R, NT>& sm, typename Quad<T>::v (&x)[R][LW / 4], int (&pos)[R],
                                              int k, int n, DeviceStatus* status, int elem) {
   constexpr int NW = NT / 64, par = KK & 1;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -160,11 +182,11 @@ __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, NT>& sm, typename 
     bpos = take ? pos[q] : bpos;
     bq = take ? q : bq;
   }
-  const T wbest = wave_max(best);
-  if (wbest < T(0)) {
+  const unsigned key = mag_key(best), kmax = wave_max(key);
+  if (kmax == 0) {
     if (lane == 0) sm.cidx[par][wv] = INT_MAX;
   } else {
-    const int win = first_lane(__ballot(best == wbest), bpos);
+    const int win = best_lane(__ballot(key == kmax), best, bpos);
     const int sq = read_lane(bq, win);
     if (lane == win) {
       put_row<LW, 0>(x, sq, KK, sm.cand[par][wv], &sm.cval[par][wv]);
@@ -172,17 +194,19 @@ __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, NT>& sm, typename 
     }
   }
   __syncthreads();
-  // the workgroup's pivot: lane w looks at wave w's candidate.  Buffers
-  // alternate by column parity: one is rewritten only after every wave has
-  // passed the next column's barrier, i.e. finished reading it.
+  // the workgroup's pivot: lane w looks at wave w's candidate (and inverts
+  // it, while the search goes on).  Buffers alternate by column parity: one
+  // is rewritten only after every wave has passed the next column's barrier,
+  // i.e. finished reading it.
   const int wl = lane & (NW - 1);
   const int ci = sm.cidx[par][wl];
-  const T cv = sm.cval[par][wl];
+  const T cv = sm.cval[par][wl], cinv = T(1) / cv;
   const T ca = ci == INT_MAX ? T(-1) : fabs(cv);
-  const T gbest = read_lane(row_max(ca), 0);
-  const int bw = first_lane(__ballot(ca == gbest) & ((1ull << NW) - 1), ci);
+  const unsigned ckey = mag_key(ca), gkey = read_lane(row_max(ckey), 0);
+  const int bw = best_lane(__ballot(ckey == gkey) & ((1ull << NW) - 1), ca, ci);
   int piv = read_lane(ci, bw);
-  T u0 = read_lane(cv, bw);
+  T rinv = read_lane(cinv, bw);
+  const T gbest = read_lane(ca, bw);
   const T* urow = sm.cand[par][bw];
   if (!(gbest > T(0)) || !isfinite(gbest)) {
     // no pivot: row k stays (the branch is uniform over the workgroup)
@@ -193,10 +217,9 @@ __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, NT>& sm, typename 
     __syncthreads();
     piv = k;
     urow = sm.krow[0];
-    u0 = sm.krow[1][0];
+    rinv = T(1) / sm.krow[1][0];
     __syncthreads();  // read before another column posts its row k
   }
-  const T rinv = T(1) / u0;
 #pragma unroll
   for (int q = 0; q < R; ++q) pos[q] = pos[q] == piv ? k : pos[q] == k ? piv : pos[q];
   // eliminate below the pivot; rows at positions <= k keep their values
@@ -233,7 +256,7 @@ __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, NT>& sm, typename 
 }
 
 template <typename T, int LW, int R, int NT, int KK>
-__device__ __forceinline__ void pivot_columns(PanelSmem<T, LW, NT>& sm, typename Quad<T>::v (&x)[R][LW / 4], int (&pos)[R],
+__device__ __forceinline__ void pivot_columns(PanelSmem<T, LW, R, NT>& sm, typename Quad<T>::v (&x)[R][LW / 4], int (&pos)[R],
                                               int cs, int sw, int n, DeviceStatus* status, int elem) {
   if constexpr (KK < LW) {
     if constexpr (KK % 4 == 0)  // sw is a multiple of 4, as n is
@@ -246,43 +269,78 @@ __device__ __forceinline__ void pivot_columns(PanelSmem<T, LW, NT>& sm, typename
 template <typename T, int LW, int R, int NT>
 __global__ __launch_bounds__(NT, NT == 512 && R * LW * sizeof(T) <= 256 ? 4 : 1)
 void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right) {
-  typedef PanelSmem<T, LW, NT> SM;
+  typedef PanelSmem<T, LW, R, NT> SM;
   typedef Mfma<T> MF;
-  constexpr int NW = NT / 64, LIS = SM::LIS, V = 16 / sizeof(T);  // values per 16-byte vector
-  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int NW = NT / 64, LIS = SM::LIS;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   SM& sm = *reinterpret_cast<SM*>(smem_raw);
-  int* prow = sm.prow;
+  const int* prow = sm.prow;
 
   const Elem<T> el = condense_elem(wk, blockIdx.x);
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = el.n, N = el.N, wp = ce - cb;
 
-  int pos[R], phys[R];  // this thread's rows: position (a label), physical row
-  T* rowp[R];
+  int pos[R];  // positions (labels) of this thread's rows
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     const int p = cb + tid + NT * q;
     pos[q] = p;
-    phys[q] = p < n && cb > 0 ? el.perm[p] : p;
-    rowp[q] = p < N ? el.lrow(p, phys[q]) : el.LU;  // slots past the last row: never stored
+    const int phys = p < n && cb > 0 ? el.perm[p] : p;
+    sm.phys[tid + NT * q] = phys;
+    sm.rowp[tid + NT * q] = p < N ? el.lrow(p, phys) : el.LU;
   }
   for (int i = tid; i < 64 * LIS; i += NT) sm.Li[i] = T(0);
   __syncthreads();
 
+  // Rows move between memory and lanes in 16-row groups: four lanes (one of
+  // each 16-lane group) share a row's LW columns, so that a wave's access
+  // covers whole segments of 16 rows and not 16 bytes of 64, and a transpose
+  // over the lane groups gives each lane its own row.
+  constexpr int CD = LW * (int)sizeof(T) / 16;  // dwords of a row per lane
+  T* const* rowp = sm.rowp + 64 * wv + li;
+  auto row_ptr = [&](int q, int g) __attribute__((always_inline)) -> T* { return rowp[NT * q + 16 * g]; };
+  // columns [col, col + LW) of slot q's rows; those at and past col + w zero
+  auto fetch = [&](int q, int col, int w, unsigned (&raw)[4][CD]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const T* src = row_ptr(q, g) + col + lg * (LW / 4);
+      const bool ok = lg * (LW / 4) < w;
+      if constexpr (CD == 2) {
+        const uint2 v = *reinterpret_cast<const uint2*>(ok ? src : src - lg * (LW / 4));
+        raw[g][0] = ok ? v.x : 0u; raw[g][1] = ok ? v.y : 0u;
+      } else {
+#pragma unroll
+        for (int d = 0; d < CD; d += 4) {
+          // (w is a multiple of 4: FP64 in runs of two may end inside LW / 4)
+          const bool okd = lg * (LW / 4) + d * 4 / (int)sizeof(T) < w;
+          const uint4 v = *reinterpret_cast<const uint4*>(okd ? src + d * 4 / sizeof(T) : src - lg * (LW / 4));
+          raw[g][d] = okd ? v.x : 0u; raw[g][d + 1] = okd ? v.y : 0u;
+          raw[g][d + 2] = okd ? v.z : 0u; raw[g][d + 3] = okd ? v.w : 0u;
+        }
+      }
+    }
+  };
+  typedef typename Quad<T>::v Q4;
+  auto to_rows = [&](unsigned (&raw)[4][CD], Q4 (&xq)[LW / 4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int d = 0; d < CD; ++d) transpose4(raw[0][d], raw[1][d], raw[2][d], raw[3][d]);
+#pragma unroll
+    for (int j = 0; j < LW; ++j) {
+      const int c = j / (LW / 4), e = j % (LW / 4);
+      if constexpr (sizeof(T) == 4) xq[j / 4][j % 4] = __uint_as_float(raw[c][e]);
+      else xq[j / 4][j % 4] = __hiloint2double((int)raw[c][2 * e + 1], (int)raw[c][2 * e]);
+    }
+  };
+
+  unsigned raw[R][4][CD];
+#pragma unroll
+  for (int q = 0; q < R; ++q) fetch(q, cb, min(LW, wp), raw[q]);
   for (int cs = cb; cs < ce; cs += LW) {
     const int sw = min(LW, ce - cs), kp = cs - cb;
-    typename Quad<T>::v x[R][LW / 4];
+    Q4 x[R][LW / 4];
 #pragma unroll
-    for (int q = 0; q < R; ++q)
-#pragma unroll
-      for (int j = 0; j < LW; j += V) {
-        vec v = vec(T(0));
-        if (j < sw) v = *reinterpret_cast<const vec*>(rowp[q] + cs + j);
-#pragma unroll
-        for (int i = 0; i < V; ++i) x[q][(j + i) / 4][(j + i) % 4] = v[i];
-      }
+    for (int q = 0; q < R; ++q) to_rows(raw[q], x[q]);
     if (kp > 0) {
       // U rows [cb, cs) of the sub-panel's columns: L_pp^{-1} X
 #pragma unroll
@@ -304,33 +362,28 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
         }
       }
       __syncthreads();
-      // the other rows: X -= L[:, cb:cs] U, 4 columns of L at a time
-#pragma unroll 2
-      for (int k0 = 0; k0 < kp; k0 += 4) {
-        T la[R][4];
+      // the other rows: X -= L[:, cb:cs] U, LW columns of L at a time (from
+      // this wave's own stores)
+      for (int k0 = 0; k0 < kp; k0 += LW) {
 #pragma unroll
-        for (int q = 0; q < R; ++q)
+        for (int q = 0; q < R; ++q) {
+          unsigned lraw[4][CD];
+          Q4 la[LW / 4];
+          __builtin_amdgcn_sched_barrier(0);  // (one slot's loads at a time: more do not fit the registers)
+          fetch(q, cb + k0, LW, lraw);
+          to_rows(lraw, la);
 #pragma unroll
-          for (int j = 0; j < 4; j += V) {
-            const vec v = *reinterpret_cast<const vec*>(rowp[q] + cb + k0 + j);
+          for (int kk = 0; kk < LW; ++kk) {
+            const T* ur = sm.Ut + (k0 + kk) * LW;
+            const T nl = -la[kk / 4][kk % 4];
+            if constexpr (sizeof(T) == 4) {
+              T u[LW / 4];
 #pragma unroll
-            for (int i = 0; i < V; ++i) la[q][j + i] = v[i];
-          }
+              for (int c = 0; c < LW / 4; ++c) u[c] = ur[(lane & 3) * (LW / 4) + c];
+              rank_one<LW, -1>(x[q], nl, u);
+            } else {
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          const T* ur = sm.Ut + (k0 + kk) * LW;
-          if constexpr (sizeof(T) == 4) {
-            T u[LW / 4];
-#pragma unroll
-            for (int c = 0; c < LW / 4; ++c) u[c] = ur[(lane & 3) * (LW / 4) + c];
-#pragma unroll
-            for (int q = 0; q < R; ++q) rank_one<LW, -1>(x[q], -la[q][kk], u);
-          } else {
-#pragma unroll
-            for (int j = 0; j < LW; ++j) {
-              const T u = ur[row_slot<LW>(j)];
-#pragma unroll
-              for (int q = 0; q < R; ++q) x[q][j / 4][j % 4] = fma(-la[q][kk], u, x[q][j / 4][j % 4]);
+              for (int j = 0; j < LW; ++j) x[q][j / 4][j % 4] = fma(nl, ur[row_slot<LW>(j)], x[q][j / 4][j % 4]);
             }
           }
         }
@@ -343,33 +396,70 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
         }
     }
     pivot_columns<T, LW, R, NT, 0>(sm, x, pos, cs, sw, n, el.status, el.id);
-    // store; the pivot rows' own columns of L, and where they are
+    const bool inverse = !wk.self || cs + LW < ce || right > 0;  // needed further
+    // where the pivot rows are, and their own columns of L
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      if (cb + tid + NT * q < N) {
-#pragma unroll
-        for (int j = 0; j < LW; j += V)
-          if (j < sw) {
-            vec v;
-#pragma unroll
-            for (int i = 0; i < V; ++i) v[i] = x[q][(j + i) / 4][(j + i) % 4];
-            *reinterpret_cast<vec*>(rowp[q] + cs + j) = v;
-          }
-      }
       const int i = pos[q] - cs;
       if (i >= 0 && i < sw) {
-        prow[kp + i] = phys[q];
+        sm.prow[kp + i] = sm.phys[tid + NT * q];
 #pragma unroll
         for (int j = 0; j < LW; ++j)
           if (j < sw) sm.Lb[i * 64 + kp + j] = j < i ? x[q][j / 4][j % 4] : T(0);
       }
     }
-    if (!wk.self || cs + LW < ce || right > 0) {  // the inverse is needed further
-      // the panel's earlier columns of them, from memory
-      sync_global();
-      for (int o = tid; o < sw * kp; o += NT) {
-        const int i = o / kp, k = o % kp;
-        sm.Lb[i * 64 + k] = el.LU[(size_t)prow[kp + i] * n + cb + k];
+    // (nothing but earlier sub-panels' stores is in flight: the wait is short,
+    // and the rows below are read by other waves than stored them)
+    sync_global();
+    constexpr int LBV = (LW * 64 + NT - 1) / NT;
+    T lb[LBV];
+    if (inverse) {  // the panel's earlier columns of the pivot rows
+#pragma unroll
+      for (int v = 0; v < LBV; ++v) {
+        const int o = tid + v * NT, i = o >> 6, k = o & 63;
+        lb[v] = i < sw && k < kp ? el.LU[(size_t)sm.prow[kp + i] * n + cb + k] : T(0);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < LW; ++j) {
+        const int c = j / (LW / 4), e = j % (LW / 4);
+        if constexpr (sizeof(T) == 4) {
+          raw[q][c][e] = __float_as_uint(x[q][j / 4][j % 4]);
+        } else {
+          raw[q][c][2 * e] = (unsigned)__double2loint(x[q][j / 4][j % 4]);
+          raw[q][c][2 * e + 1] = (unsigned)__double2hiint(x[q][j / 4][j % 4]);
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < CD; ++d) transpose4(raw[q][0][d], raw[q][1][d], raw[q][2][d], raw[q][3][d]);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        if (cb + NT * q + 64 * wv + 16 * g + li >= N) continue;
+        T* dst = row_ptr(q, g) + cs + lg * (LW / 4);
+        if constexpr (CD == 2) {
+          if (lg * (LW / 4) < sw) *reinterpret_cast<uint2*>(dst) = make_uint2(raw[q][g][0], raw[q][g][1]);
+        } else {
+#pragma unroll
+          for (int d = 0; d < CD; d += 4)
+            if (lg * (LW / 4) + d * 4 / (int)sizeof(T) < sw)
+              *reinterpret_cast<uint4*>(dst + d * 4 / sizeof(T)) =
+                  make_uint4(raw[q][g][d], raw[q][g][d + 1], raw[q][g][d + 2], raw[q][g][d + 3]);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (cs + LW < ce) {  // the next sub-panel's columns, while the inverse grows
+#pragma unroll
+      for (int q = 0; q < R; ++q) fetch(q, cs + LW, min(LW, ce - cs - LW), raw[q]);
+    }
+    if (inverse) {
+#pragma unroll
+      for (int v = 0; v < LBV; ++v) {
+        const int o = tid + v * NT, i = o >> 6, k = o & 63;
+        if (i < sw && k < kp) sm.Lb[i * 64 + k] = lb[v];
       }
       __syncthreads();
       grow_inverse<T, LW>(sm.Li, LIS, sm.Lb, sm.Xu, kp, sw);
@@ -377,7 +467,7 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
   }
 #pragma unroll
   for (int q = 0; q < R; ++q)
-    if (cb + tid + NT * q < n) el.perm[pos[q]] = phys[q];
+    if (cb + tid + NT * q < n) el.perm[pos[q]] = sm.phys[tid + NT * q];
 
   if constexpr (sizeof(T) == 4) {
     if (right > 0) {
@@ -422,7 +512,7 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
 
 template <typename T, int LW, int R, int NT>
 static hipError_t launch_panel(const CondenseWork<T>& w, int c0, int cb, int ce, int right, hipStream_t s) {
-  size_t smem = (sizeof(PanelSmem<T, LW, NT>) + 15) & ~size_t(15);
+  size_t smem = (sizeof(PanelSmem<T, LW, R, NT>) + 15) & ~size_t(15);
   if (cb != c0 && !w.self) smem += sizeof(T) * 64 * 65;
   auto k = condense_panel_kernel<T, LW, R, NT>;
   if (smem > 64 * 1024) {
