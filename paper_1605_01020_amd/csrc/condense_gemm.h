@@ -39,7 +39,7 @@
 namespace iedg {
 
 constexpr int GT = 256;  // threads per workgroup of the tile kernels (4 waves)
-constexpr int KC = 16;   // k-slab depth
+constexpr int KC = 32;   // k-slab depth
 
 // Round to nearest even FP32 -> BF16 (bit pattern); NaN stays NaN.
 __device__ __forceinline__ unsigned to_bf16(float f) {
@@ -52,17 +52,23 @@ typedef short bf16x4 __attribute__((ext_vector_type(4)));
 
 // ---- the tile engine --------------------------------------------------------
 // acc += (-L) U over k for a workgroup's TM x TN tile, operands through LDS in
-// slabs of KC, the next slab's loads in flight while one is multiplied.
-// Every entry takes its products in ascending k, four (BF16: 16) per MFMA,
-// so neither the tile shape nor the order of the phases shows in the result.
-// Waves are 2 x 2, or with COLS all along columns (each wave then holds every
-// row of its columns, which the panel-row triangular solve needs).
+// slabs of KC, the next slab's loads in flight in registers while one is
+// multiplied.  Every entry takes its products in ascending k, four (BF16: 16)
+// per MFMA, so neither the tile shape nor the order of the phases shows in the
+// result.  Waves are 2 x 2, or with COLS all along columns (each wave then
+// holds every row of its columns, which the panel-row triangular solve needs).
 //
-// LDS, MM = 0: slabs k-major, A at As[k][row ^ 16 ((k & 3) ^ (k >> 2))], B at
+// What bounds it: the matrix cores, once the loads are covered.  L is read a
+// row at a time with rows far apart, so a slab is as deep as a cache line of
+// FP32 is long (16 deep, two slabs in LDS, left waves waiting 58% of the time
+// and the matrix cores busy 48%); one slab of that depth in LDS, and the next
+// in registers, keeps four FP32 workgroups a CU.
+//
+// LDS, MM = 0: slabs k-major, A at As[k][row ^ swizzle(k)], B at
 // Bs[k][col ^ 16 (k & 3)]: the four k of a fragment read then lie in
 // different banks, and so do the k of a vector write.  MM = 1: BF16,
-// row-major with 16 k per row, As[row][4 (g ^ s) + k % 4] for k group
-// g = k / 4, s = 2 at rows with bit 3 set: a fragment is one 8-byte read.
+// row-major with KC k per row, k group g = k / 4 of a row at g ^ 2 (row / 4 % 4):
+// a fragment is one 8-byte read.
 template <typename T, int MM, int TM, int TN, bool COLS>
 struct Tile {
   static constexpr int WR = COLS ? 1 : 2, WC = 4 / WR;
@@ -73,7 +79,7 @@ struct Tile {
   static constexpr int BL = TN * KC / (BC * GT);      // B loads per thread and slab
   static constexpr int ES = MM ? 2 : (int)sizeof(T);  // bytes per LDS value
   static constexpr int STAGE = KC * (TM + TN) * ES;   // bytes
-  static_assert(AL >= 1 && BL >= 1 && (MM == 0 || BL == 4), "tile shape");
+  static_assert(AL >= 1 && BL >= 1 && (MM == 0 || BL == 8), "tile shape");
 
   typedef typename Mfma<T>::acc_t acc_t;
   typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
@@ -106,9 +112,10 @@ struct Tile {
   static __device__ __forceinline__ int a_k() { return V * (threadIdx.x % (KC / V)); }
   static __device__ __forceinline__ int b_col() { return BC * (threadIdx.x % (TN / BC)); }
   static __device__ __forceinline__ int b_k(int q) {
-    return MM ? 4 * (threadIdx.x / (TN / BC)) + q : threadIdx.x / (TN / BC) + q * (GT / (TN / BC));
+    return MM ? 4 * (threadIdx.x / (TN / BC) + 4 * (q >> 2)) + (q & 3) : threadIdx.x / (TN / BC) + q * (GT / (TN / BC));
   }
 
+  static __device__ __forceinline__ int swizzle(int k) { return 16 * ((k ^ (k >> 2)) & 3) ^ 8 * ((k >> 4) & 1); }
   struct Slab {
     vec a[AL];
     bvec b[BL];
@@ -153,7 +160,7 @@ struct Tile {
 #pragma unroll
         for (int i = 0; i < V; ++i) {
           const int k = a_k() + i;
-          As[k * TM + (a_row(q) ^ (16 * ((k & 3) ^ (k >> 2))))] = -s.a[q][i];  // L enters negated
+          As[k * TM + (a_row(q) ^ swizzle(k))] = -s.a[q][i];  // L enters negated
         }
 #pragma unroll
       for (int q = 0; q < BL; ++q) {
@@ -165,7 +172,7 @@ struct Tile {
       unsigned* Bs = As + KC * TM / 2;
 #pragma unroll
       for (int q = 0; q < AL; ++q) {
-        const int row = a_row(q), g = (a_k() >> 2) ^ (((row >> 3) & 1) << 1);
+        const int row = a_row(q), g = (a_k() >> 2) ^ (((row >> 2) & 3) << 1);
         uint2 v;
         v.x = to_bf16(-s.a[q][0]) | (to_bf16(-s.a[q][1]) << 16);
         v.y = to_bf16(-s.a[q][2]) | (to_bf16(-s.a[q][3]) << 16);
@@ -173,25 +180,32 @@ struct Tile {
       }
 #pragma unroll
       for (int c = 0; c < BC; ++c) {
-        const int col = b_col() + c, g = (b_k(0) >> 2) ^ (((col >> 3) & 1) << 1);
-        uint2 v;
-        v.x = to_bf16(s.b[0][c]) | (to_bf16(s.b[1][c]) << 16);
-        v.y = to_bf16(s.b[2][c]) | (to_bf16(s.b[3][c]) << 16);
-        *reinterpret_cast<uint2*>(Bs + col * (KC / 2) + 2 * g) = v;
+        const int col = b_col() + c, sw = ((col >> 2) & 3) << 1;
+#pragma unroll
+        for (int q = 0; q < BL; q += 4) {
+          const int g = (b_k(q) >> 2) ^ sw;
+          uint2 v;
+          v.x = to_bf16(s.b[q][c]) | (to_bf16(s.b[q + 1][c]) << 16);
+          v.y = to_bf16(s.b[q + 2][c]) | (to_bf16(s.b[q + 3][c]) << 16);
+          *reinterpret_cast<uint2*>(Bs + col * (KC / 2) + 2 * g) = v;
+        }
       }
     }
   }
   static __device__ __forceinline__ void mma(const unsigned char* stage, int wr0, int wc0, acc_t (&acc)[RB][CB]) {
     const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
     if constexpr (MM == 0) {
-      const T* As = reinterpret_cast<const T*>(stage) + lg * TM + wr0 + li;
+      const T* As = reinterpret_cast<const T*>(stage) + lg * TM + wr0;
       const T* Bs = reinterpret_cast<const T*>(stage) + KC * TM + lg * TN + li;
 #pragma unroll
       for (int ks = 0; ks < KC / 4; ++ks) {
+        // two k-steps' fragments at a time: all of a slab's would not fit
+        // beside the accumulators and the next slab's loads
+        if (ks % 2 == 0) __builtin_amdgcn_sched_barrier(0);
         T av[RB], bv[CB];
         // (wr0 is a multiple of 64: the swizzle stays inside 64 rows)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) av[rb] = As[4 * ks * TM + 64 * (rb >> 2) + 16 * ((rb ^ ks ^ lg) & 3)];
+        for (int rb = 0; rb < RB; ++rb) av[rb] = As[4 * ks * TM + 64 * (rb >> 2) + 16 * ((rb ^ ks ^ lg) & 3) + (li ^ (8 * (ks >> 2)))];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) bv[cb] = Bs[4 * ks * TN + ((wc0 + 16 * cb) ^ (16 * lg))];
 #pragma unroll
@@ -200,40 +214,38 @@ struct Tile {
           for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = Mfma<T>::mac(av[rb], bv[cb], acc[rb][cb]);
       }
     } else {
-      const int g = lg ^ ((li >> 3) << 1);
-      const unsigned* As = reinterpret_cast<const unsigned*>(stage) + (wr0 + li) * (KC / 2) + 2 * g;
-      const unsigned* Bs = reinterpret_cast<const unsigned*>(stage) + KC * TM / 2 + (wc0 + li) * (KC / 2) + 2 * g;
-      bf16x4 av[RB], bv[CB];
+      const unsigned* As = reinterpret_cast<const unsigned*>(stage) + (wr0 + li) * (KC / 2);
+      const unsigned* Bs = reinterpret_cast<const unsigned*>(stage) + KC * TM / 2 + (wc0 + li) * (KC / 2);
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) av[rb] = *reinterpret_cast<const bf16x4*>(As + 16 * rb * (KC / 2));
+      for (int ks = 0; ks < KC / 16; ++ks) {
+        const int g = (4 * ks + lg) ^ ((li >> 2) << 1);
+        bf16x4 av[RB], bv[CB];
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) bv[cb] = *reinterpret_cast<const bf16x4*>(Bs + 16 * cb * (KC / 2));
+        for (int rb = 0; rb < RB; ++rb) av[rb] = *reinterpret_cast<const bf16x4*>(As + 16 * rb * (KC / 2) + 2 * g);
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+        for (int cb = 0; cb < CB; ++cb) bv[cb] = *reinterpret_cast<const bf16x4*>(Bs + 16 * cb * (KC / 2) + 2 * g);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[rb], bv[cb], acc[rb][cb], 0, 0, 0);
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb)
+            acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[rb], bv[cb], acc[rb][cb], 0, 0, 0);
+      }
     }
   }
   // acc += (-L) U for k in [0, K), K > 0; sp[k]: physical row of U's row k.
-  // lds: two stages.  Starts with every thread past the last use of lds.
+  // lds: one slab.  Starts with every thread past the last use of lds.
   template <bool TAIL>
   static __device__ __forceinline__ void product(const Ops& o, const unsigned short* sp, int K, unsigned char* lds,
                                                  int wr0, int wc0, acc_t (&acc)[RB][CB]) {
     Slab s;
     load<TAIL>(o, sp, 0, K, s);
-    store<TAIL>(o, lds, s, 0, K);
-    __syncthreads();
-    const int nch = (K + KC - 1) / KC;
-    int cur = 0;
-    for (int ch = 1; ch < nch; ++ch) {
-      load<TAIL>(o, sp, ch * KC, K, s);
-      mma(lds + cur, wr0, wc0, acc);
-      cur ^= STAGE;
-      store<TAIL>(o, lds + cur, s, ch * KC, K);
+    for (int k0 = 0; k0 < K; k0 += KC) {
+      store<TAIL>(o, lds, s, k0, K);
+      __syncthreads();
+      if (k0 + KC < K) load<TAIL>(o, sp, k0 + KC, K, s);
+      mma(lds, wr0, wc0, acc);
       __syncthreads();
     }
-    mma(lds + cur, wr0, wc0, acc);
   }
 };
 
@@ -242,6 +254,14 @@ struct Tile {
 __device__ __forceinline__ int opaque(int v) {
   asm volatile("" : "+v"(v));
   return v;
+}
+
+// Between the row blocks of a tile's inputs.  FP32 storage: two row blocks'
+// FP64 inputs in flight, as more would set the kernel's registers (and so the
+// waves a SIMD holds) by its first microseconds.
+template <typename T>
+__device__ __forceinline__ void input_step(int rb) {
+  if (sizeof(T) == 4 && rb % 2 == 0) __builtin_amdgcn_sched_barrier(0);
 }
 
 // Row map of a launch in LDS: sp[k] for U's rows (positions kb .. kb+K-1) and
@@ -270,7 +290,7 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_col_kerne
   if (!condense_locate(wk, tiles, it, tile)) return;
   const Elem<T> el = condense_elem(wk, it);
   const int n = el.n, K = c0 - kb, r0 = c0 + 128 * tile;
-  unsigned short* rp = reinterpret_cast<unsigned short*>(lds + 2 * TL::STAGE);
+  unsigned short* rp = reinterpret_cast<unsigned short*>(lds + TL::STAGE);
   unsigned short* sp = rp + 128;
   load_row_map<128>(el.perm, c0 == 0, n, kb, K, r0, sp, rp);
   int lane = threadIdx.x & 63;
@@ -280,7 +300,8 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_col_kerne
 
   typename TL::acc_t acc[TL::RB][TL::CB];
 #pragma unroll
-  for (int rb = 0; rb < TL::RB; ++rb)
+  for (int rb = 0; rb < TL::RB; ++rb) {
+    input_step<T>(rb);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int i = wr0 + 16 * rb + Mfma<T>::row(lane, v), row = r0 + i;
@@ -300,6 +321,7 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_col_kerne
         }
       }
     }
+  }
   if (K > 0) {
     typename TL::Ops o;
 #pragma unroll
@@ -331,6 +353,40 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_col_kerne
 // Tiles 0 .. tiles0-1 cover columns [c1, n) of U, the others the t columns of
 // U12 and, at column t, the right-hand side w.
 // SELF: L_pp^{-1} is formed here from the panel's L instead of read.
+// The solve takes L_pp^{-1} in 16 x 16 blocks from LDS (over the slab, which is
+// done by then): read from memory where needed, block by block, its latency
+// was most of the kernel's time in the first panels.
+template <typename T, int CT>
+struct InvBlocks {
+  static constexpr int NB = CT / 16, COUNT = NB * (NB + 1) / 2;  // on and below the diagonal
+  static constexpr size_t BYTES = sizeof(T) * 256 * COUNT;
+  static __device__ __forceinline__ int at(int ib, int rb) { return (ib * (ib + 1) / 2 + rb) * 256; }
+  // entry (r, c) of a block: runs of four columns swizzled by the row, so
+  // that a fragment's lanes fall into different banks
+  static __device__ __forceinline__ int entry(int r, int c) {
+    return r * 16 + (c ^ (4 * (sizeof(T) == 4 ? (r >> 2) & 3 : (r >> 1) & 3)));
+  }
+  // inv: 64 x 64 blocks as the panel kernel writes them (memory or LDS)
+  static __device__ __forceinline__ void stage(const T* inv, T* dst) {
+    typedef T vec4 __attribute__((ext_vector_type(4)));
+    for (int o = threadIdx.x; o < COUNT * 64; o += GT) {
+      const int b = o >> 6, r = (o >> 2) & 15, c = 4 * (o & 3);
+      int ib = 0;
+      while ((ib + 1) * (ib + 2) / 2 <= b) ++ib;
+      const int rb = b - ib * (ib + 1) / 2;
+      const vec4 v = *reinterpret_cast<const vec4*>(inv + ((ib >> 2) + (rb >> 2)) * kInvBlock + (16 * (ib & 3) + r) * 64 +
+                                                    16 * (rb & 3) + c);
+      *reinterpret_cast<vec4*>(dst + b * 256 + entry(r, c)) = v;
+    }
+    __syncthreads();
+  }
+};
+
+template <typename T, int MM, int CT>
+constexpr int row_slab() {
+  return std::max<int>(Tile<T, MM, CT, 128, true>::STAGE, (int)InvBlocks<T, CT>::BYTES);
+}
+
 template <typename T, int MM, int CT, int LW, bool SELF>
 __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kernel(CondenseWork<T> wk, int tiles, int tiles0,
                                                                                int c0, int c1) {
@@ -346,7 +402,7 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kerne
   const int j0 = seg ? TN * (tile - tiles0) : c1 + TN * tile;
   const int width = seg ? t : n, jl = seg && el.F ? t + 1 : width;
   if (j0 >= jl) return;
-  unsigned short* rp = reinterpret_cast<unsigned short*>(lds + 2 * TL::STAGE);
+  unsigned short* rp = reinterpret_cast<unsigned short*>(lds + row_slab<T, MM, CT>());
   unsigned short* sp = rp + CT;
   load_row_map<CT>(el.perm, false, n, 0, c0, c0, sp, rp);
   int lane = tid & 63;
@@ -356,7 +412,7 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kerne
   const T* inv = el.Ke;
   if constexpr (SELF) {
     // as the panel kernel grows it, from the stored L
-    T* Li = reinterpret_cast<T*>(lds + 2 * TL::STAGE + 2 * ((CT + c0 + 7) & ~7));
+    T* Li = reinterpret_cast<T*>(lds + row_slab<T, MM, CT>() + 2 * ((CT + c0 + 7) & ~7));
     T* Lb = Li + (CT == 128 ? 3 : 1) * kInvBlock;
     T* Y = Lb + LW * 64;
     for (int i = tid; i < (CT == 128 ? 3 : 1) * kInvBlock; i += GT) Li[i] = T(0);
@@ -383,7 +439,8 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kerne
   typename TL::acc_t acc[TL::RB][TL::CB];
   const double* in = seg ? el.B : el.A;
 #pragma unroll
-  for (int rb = 0; rb < TL::RB; ++rb)
+  for (int rb = 0; rb < TL::RB; ++rb) {
+    input_step<T>(rb);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int i = 16 * rb + MF::row(lane, v);
@@ -396,6 +453,7 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kerne
         acc[rb][cb][v] = x;
       }
     }
+  }
   if (c0 > 0) {
     typename TL::Ops o;
 #pragma unroll
@@ -412,6 +470,9 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kerne
 #pragma unroll
           for (int cb = 0; cb < TL::CB; ++cb) acc[rb][cb][v] = T(0);
   }
+  typedef InvBlocks<T, CT> IB;
+  T* ib_lds = reinterpret_cast<T*>(lds);
+  IB::stage(inv, ib_lds);
 #pragma unroll
   for (int ib = TL::RB - 1; ib >= 0; --ib) {
     if (16 * ib >= wp) continue;
@@ -420,10 +481,10 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kerne
     for (int cb = 0; cb < TL::CB; ++cb) nacc[cb] = MF::zero();
 #pragma unroll
     for (int rb = 0; rb <= ib; ++rb) {
-      const T* blk = inv + ((ib >> 2) + (rb >> 2)) * kInvBlock + (16 * (ib & 3) + li) * 64 + 16 * (rb & 3);
+      const T* blk = ib_lds + IB::at(ib, rb);
       T av[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) av[v] = blk[MF::row(lane, v)];
+      for (int v = 0; v < 4; ++v) av[v] = blk[IB::entry(li, MF::row(lane, v))];
 #pragma unroll
       for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -461,7 +522,7 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_schur_ker
   const int n = el.n, t = el.t, jl = el.F ? t + 1 : t;
   const int r0 = 128 * (tile / ctiles), j0 = TN * (tile % ctiles);
   if (j0 >= jl) return;
-  unsigned short* sp = reinterpret_cast<unsigned short*>(lds + 2 * TL::STAGE);
+  unsigned short* sp = reinterpret_cast<unsigned short*>(lds + TL::STAGE);
   load_row_map<128>(el.perm, false, n, 0, n, -1, sp, nullptr);
   int lane = threadIdx.x & 63;
   const int li = lane & 15;
@@ -469,7 +530,8 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_schur_ker
   const int wr0 = (wv % TL::WR) * TL::WM, wc0 = (wv / TL::WR) * TL::WN;
   typename TL::acc_t acc[TL::RB][TL::CB];
 #pragma unroll
-  for (int rb = 0; rb < TL::RB; ++rb)
+  for (int rb = 0; rb < TL::RB; ++rb) {
+    input_step<T>(rb);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int row = r0 + wr0 + 16 * rb + Mfma<T>::row(lane, v);
@@ -479,6 +541,7 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_schur_ker
         acc[rb][cb][v] = (row < t && j < t) ? (T)el.D[(size_t)row * t + j] : T(0);
       }
     }
+  }
   typename TL::Ops o;
 #pragma unroll
   for (int q = 0; q < TL::AL; ++q)
@@ -512,7 +575,7 @@ template <typename T, int MM, int TN, int HALF>
 hipError_t launch_col(const CondenseWork<T>& w, int c0, int c1, int kb, hipStream_t s) {
   typedef Tile<T, MM, 128, TN, false> TL;
   const int tiles = (w.n + w.t - c0 + 127) / 128;
-  const size_t smem = 2 * TL::STAGE + sizeof(unsigned short) * (128 + (c0 - kb));
+  const size_t smem = TL::STAGE + sizeof(unsigned short) * (128 + (c0 - kb));
   auto k = condense_col_kernel<T, MM, TN, HALF>;
   hipError_t e = launch_lds(reinterpret_cast<const void*>(k), smem);
   if (e != hipSuccess) return e;
@@ -522,9 +585,8 @@ hipError_t launch_col(const CondenseWork<T>& w, int c0, int c1, int kb, hipStrea
 
 template <typename T, int MM, int CT, int LW, bool SELF>
 hipError_t launch_row(const CondenseWork<T>& w, int c0, int c1, hipStream_t s) {
-  typedef Tile<T, MM, CT, 128, true> TL;
   const int tiles0 = (w.n - c1 + 127) / 128, tiles = tiles0 + w.t / 128 + 1;  // t + 1 columns with w
-  size_t smem = 2 * TL::STAGE + sizeof(unsigned short) * ((CT + c0 + 7) & ~7);
+  size_t smem = row_slab<T, MM, CT>() + sizeof(unsigned short) * ((CT + c0 + 7) & ~7);
   if (SELF) smem += sizeof(T) * (CT == 128 ? 3 * kInvBlock + LW * 64 + 64 * 65 : kInvBlock + 2 * LW * 64);
   auto k = condense_row_kernel<T, MM, CT, LW, SELF>;
   hipError_t e = launch_lds(reinterpret_cast<const void*>(k), smem);
@@ -537,7 +599,7 @@ template <typename T, int MM, int TN>
 hipError_t launch_schur(const CondenseWork<T>& w, hipStream_t s) {
   typedef Tile<T, MM, 128, TN, false> TL;
   const int ctiles = w.t / TN + 1, tiles = (w.t + 127) / 128 * ctiles;  // t + 1 columns with r
-  const size_t smem = 2 * TL::STAGE + sizeof(unsigned short) * w.n;
+  const size_t smem = TL::STAGE + sizeof(unsigned short) * w.n;
   auto k = condense_schur_kernel<T, MM, TN>;
   hipError_t e = launch_lds(reinterpret_cast<const void*>(k), smem);
   if (e != hipSuccess) return e;
