@@ -366,13 +366,15 @@ struct InvBlocks {
   static __device__ __forceinline__ int entry(int r, int c) {
     return r * 16 + (c ^ (4 * (sizeof(T) == 4 ? (r >> 2) & 3 : (r >> 1) & 3)));
   }
-  // inv: 64 x 64 blocks as the panel kernel writes them (memory or LDS)
-  static __device__ __forceinline__ void stage(const T* inv, T* dst) {
+  // inv: 64 x 64 blocks as the panel kernel writes them (memory or LDS); only
+  // the wp rows of the panel's own are there
+  static __device__ __forceinline__ void stage(const T* inv, T* dst, int wp) {
     typedef T vec4 __attribute__((ext_vector_type(4)));
     for (int o = threadIdx.x; o < COUNT * 64; o += GT) {
       const int b = o >> 6, r = (o >> 2) & 15, c = 4 * (o & 3);
       int ib = 0;
       while ((ib + 1) * (ib + 2) / 2 <= b) ++ib;
+      if (16 * ib >= wp) break;
       const int rb = b - ib * (ib + 1) / 2;
       const vec4 v = *reinterpret_cast<const vec4*>(inv + ((ib >> 2) + (rb >> 2)) * kInvBlock + (16 * (ib & 3) + r) * 64 +
                                                     16 * (rb & 3) + c);
@@ -472,7 +474,7 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kerne
   }
   typedef InvBlocks<T, CT> IB;
   T* ib_lds = reinterpret_cast<T*>(lds);
-  IB::stage(inv, ib_lds);
+  IB::stage(inv, ib_lds, wp);
 #pragma unroll
   for (int ib = TL::RB - 1; ib >= 0; --ib) {
     if (16 * ib >= wp) continue;
