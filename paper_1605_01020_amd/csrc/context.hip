@@ -112,6 +112,9 @@ iedg_status build_pattern(iedg_context ctx, iedg_mesh_s* m, const std::vector<st
   if (st == IEDG_OK) st = upload(ctx, &m->d_col_face, m->col_face);
   if (st == IEDG_OK) st = upload(ctx, &m->d_diag_slot, diag_slot);
   if (st == IEDG_OK) st = upload(ctx, &m->d_level_rows, m->level_rows);
+  std::vector<int4> desc;
+  for (int i : m->level_rows) desc.push_back(make_int4(m->order[i], m->row_ptr[i], diag_slot[i], m->row_ptr[i + 1]));
+  if (st == IEDG_OK) st = upload(ctx, &m->d_level_desc, desc);
   if (st == IEDG_OK) st = upload(ctx, &m->d_ilu_lptr, lptr);
   if (st == IEDG_OK) st = upload(ctx, &m->d_ilu_l, lslots);
   if (st == IEDG_OK) st = upload(ctx, &m->d_ilu_uptr, uptr);
@@ -371,6 +374,7 @@ void iedg_mesh_destroy(iedg_mesh m) {
                      m->d_ilu_lptr, m->d_ilu_l, m->d_ilu_uptr, m->d_ilu_upd};
   for (int32_t* p : ptrs)
     if (p) hipFree(p);
+  if (m->d_level_desc) hipFree(m->d_level_desc);
   if (m->d_rwork) hipFree(m->d_rwork);
   delete m;
 }

@@ -33,6 +33,8 @@ struct iedg_mesh_s {
   int32_t* d_col_face = nullptr;    // [nnzb]
   int32_t* d_diag_slot = nullptr;   // [n_face]
   int32_t* d_level_rows = nullptr;  // [n_face]
+  // [n_face], as level_rows: unit, first slot, diagonal slot, end of slots
+  int4* d_level_desc = nullptr;
   // assembly of K: block s receives Ke_e[a][c] for every code e*S*S + a*S + c
   // in asm_list[asm_ptr[s] .. asm_ptr[s+1]) (ascending: e, then a, then c)
   int32_t* d_asm_ptr = nullptr;     // [nnzb + 1]

@@ -92,41 +92,70 @@ __global__ void assemble_r_kernel(int n_face, int b, int t, int S, const int32_t
 }
 
 // ---- BSR products --------------------------------------------------------
-// Threads form G = STHR / b groups of b lanes; lane rr of group g
-// accumulates row rr over blocks g, g+G, ... of a slot range.  Reads of a
+// A workgroup of THR threads forms G = THR / b groups of b lanes; lane rr of a
+// group accumulates row rr over its share of a slot range.  Reads of a
 // column-major block by consecutive rr are contiguous.
-template <typename T>
+// CS = 0: a group takes blocks g, g + G, ..., eight columns per round trip.
+//   Where many rows run at a time this is bound by HBM (FP32 / FP64 SpMV of
+//   6,656 rows of b = 80: 5.2 / 5.4 TB/s).
+// CS > 0: the share is units of CS columns of a block, a unit's loads all
+//   issued together.  Where few rows run at a time (a level of a small mesh
+//   has some tens) a row's time is its chain of memory round trips, and short
+//   units on more threads make it one or two rounds: 40 rows of b = 45 a level
+//   took 8.3 us in the other form and take 6.0; where the GPU is full the units
+//   cost more than they save (FP32, 6,656 rows: 336 -> 455 us).
+constexpr int PTHR = 512;
+constexpr int kManyRows = 512;  // two workgroups a CU
+template <typename T, int CS>
 __device__ inline double block_row_sum(int b, const T* blocks, const int32_t* col_face, int s0, int s1,
                                        const double* x, int g, int G, int rr) {
   double acc = 0.0;
   if (g >= G) return 0.0;
-  for (int s = s0 + g; s < s1; s += G) {
-    const T* blk = blocks + (size_t)s * b * b + rr;
-    const double* xs = x + (size_t)col_face[s] * b;
-    // eight columns per round trip: eight block loads (contiguous across the
-    // group's lanes) and eight vector loads in flight per lane
-    double a[8];
+  if constexpr (CS == 0) {
+    for (int s = s0 + g; s < s1; s += G) {
+      const T* blk = blocks + (size_t)s * b * b + rr;
+      const double* xs = x + (size_t)col_face[s] * b;
+      double a[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) a[u] = 0.0;
-    int cc = 0;
-    for (; cc + 8 <= b; cc += 8) {
-      T m[8];
-      double xv[8];
+      for (int u = 0; u < 8; ++u) a[u] = 0.0;
+      int cc = 0;
+      for (; cc + 8 <= b; cc += 8) {
+        T m[8];
+        double xv[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        m[u] = blk[(size_t)(cc + u) * b];
-        xv[u] = xs[cc + u];
+        for (int u = 0; u < 8; ++u) {
+          m[u] = blk[(size_t)(cc + u) * b];
+          xv[u] = xs[cc + u];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] += (double)m[u] * xv[u];
       }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] += (double)m[u] * xv[u];
+      for (; cc < b; ++cc) a[0] += (double)blk[(size_t)cc * b] * xs[cc];
+      acc += ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
     }
-    for (; cc < b; ++cc) a[0] += (double)blk[(size_t)cc * b] * xs[cc];
-    acc += ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+  } else {
+    const int nseg = (b + CS - 1) / CS, units = (s1 - s0) * nseg;
+    for (int u = g; u < units; u += G) {
+      const int s = s0 + u / nseg, c0 = (u % nseg) * CS, cnt = min(CS, b - c0);
+      const T* blk = blocks + (size_t)s * b * b + (size_t)c0 * b + rr;
+      const double* xs = x + (size_t)col_face[s] * b + c0;
+      T m[CS];
+      double xv[CS];
+      // (past the block's last column its entries are read again and dropped)
+#pragma unroll
+      for (int q = 0; q < CS; ++q) m[q] = blk[(size_t)min(q, cnt - 1) * b];
+#pragma unroll
+      for (int q = 0; q < CS; ++q) xv[q] = xs[min(q, cnt - 1)];
+      double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < CS; ++q) a[q & 3] = q < cnt ? a[q & 3] + (double)m[q] * xv[q] : a[q & 3];
+      acc += (a[0] + a[1]) + (a[2] + a[3]);
+    }
   }
   return acc;
 }
 
-// Reduce the G group partials of row rr into red[rr]; fixed order.
+// Reduce the G group partials of row rr into red[G b + rr]; fixed order.
 __device__ inline void group_reduce(double* red, int b, int G, int g, int rr, double v) {
   if (g < G) red[g * b + rr] = v;
   __syncthreads();
@@ -139,15 +168,15 @@ __device__ inline void group_reduce(double* red, int b, int G, int g, int rr, do
 }
 
 // y = K x  (mode 0)   or   y = rhs - K x  (mode 1)
-template <typename T>
-__global__ __launch_bounds__(STHR) void spmv_kernel(int b, const int32_t* row_face, const int32_t* row_ptr,
-                                                    const int32_t* col_face, const T* K, const double* x,
-                                                    const double* rhs, double* y, int mode, const int* skip) {
-  __shared__ double red[STHR + 128];
+template <typename T, int CS, int THR>
+__global__ __launch_bounds__(THR) void spmv_kernel(int b, const int32_t* row_face, const int32_t* row_ptr,
+                                                   const int32_t* col_face, const T* K, const double* x,
+                                                   const double* rhs, double* y, int mode, const int* skip) {
+  __shared__ double red[THR + 128];
   if (skip && *skip) return;
   const int i = blockIdx.x;
-  const int G = STHR / b, g = threadIdx.x / b, rr = threadIdx.x % b;
-  const double v = block_row_sum<T>(b, K, col_face, row_ptr[i], row_ptr[i + 1], x, g, G, rr);
+  const int G = THR / b, g = threadIdx.x / b, rr = threadIdx.x % b;
+  const double v = block_row_sum<T, CS>(b, K, col_face, row_ptr[i], row_ptr[i + 1], x, g, G, rr);
   group_reduce(red, b, G, g, rr, v);
   if (threadIdx.x < b) {
     const size_t o = (size_t)row_face[i] * b + threadIdx.x;
@@ -156,7 +185,8 @@ __global__ __launch_bounds__(STHR) void spmv_kernel(int b, const int32_t* row_fa
   }
 }
 
-// One level of the BILU(0) sweeps (rows[n_copy ..] of the launch):
+// One level of the BILU(0) sweeps (rows[n_copy ..] of the launch; a row is
+// its unit, first slot, diagonal slot and end of slots):
 //   mode 0, forward:           y_i = x_i - sum over lower slots L_ik v_k;
 //   mode 1, backward:          y_i = Uinv_i (y_i - sum over upper slots U_ij v_j);
 //   mode 2, forward + inverse: y_i = Uinv_i (x_i - sum over lower slots L_ik v_k),
@@ -165,48 +195,57 @@ __global__ __launch_bounds__(STHR) void spmv_kernel(int b, const int32_t* row_fa
 // values equal x).  The first n_copy workgroups copy y_i = x_i for the rows
 // of level 0, which have no lower slots, so that level 0 and level 1 share a
 // launch.  x may equal y.
-template <typename T>
-__global__ __launch_bounds__(STHR) void sweep_kernel(int b, const int32_t* rows, const int32_t* row_face,
-                                                     const int32_t* row_ptr, const int32_t* diag_slot,
-                                                     const int32_t* col_face, const T* M, const double* x,
-                                                     double* y, const double* v, int mode, int n_copy,
-                                                     const int* skip) {
-  __shared__ double red[STHR + 128];
+template <typename T, int CS, int THR>
+__global__ __launch_bounds__(THR) void sweep_kernel(int b, const int4* rows, const int32_t* col_face, const T* M,
+                                                    const double* x, double* y, const double* v, int mode,
+                                                    int n_copy, const int* skip) {
+  __shared__ double red[THR + 128];
+  const int4 row = rows[blockIdx.x];
   if (skip && *skip) return;
-  const int i = rows[blockIdx.x];
-  const size_t o = (size_t)row_face[i] * b;
+  const size_t o = (size_t)row.x * b;
   if ((int)blockIdx.x < n_copy) {
     if (x != y && threadIdx.x < b) y[o + threadIdx.x] = x[o + threadIdx.x];
     return;
   }
-  const int G = STHR / b, g = threadIdx.x / b, rr = threadIdx.x % b;
-  const int ds = diag_slot[i];
-  const int s0 = mode == 1 ? ds + 1 : row_ptr[i];
-  const int s1 = mode == 1 ? row_ptr[i + 1] : ds;
-  const double* base = mode == 1 ? y : x;
-  const double sum = block_row_sum<T>(b, M, col_face, s0, s1, v, g, G, rr);
+  const int G = THR / b, g = threadIdx.x / b, rr = threadIdx.x % b;
+  const int ds = row.z;
+  const int s0 = mode == 1 ? ds + 1 : row.y;
+  const int s1 = mode == 1 ? row.w : ds;
+  // this group's columns g, g + G, ... of the inverted pivot block; where few
+  // rows run they are read while the sum does
+  constexpr int NI = CS == 0 ? 0 : CS < 16 ? 1 : 16;
+  T inv[NI + 1];
+  const T* dblk = M + (size_t)ds * b * b + rr;
+  if (mode != 0 && g < G) {
+#pragma unroll
+    for (int u = 0; u < NI; ++u) inv[u] = g + u * G < b ? dblk[(size_t)(g + u * G) * b] : T(0);
+  }
+  const double base = threadIdx.x < b ? (mode == 1 ? y : x)[o + threadIdx.x] : 0.0;
+  const double sum = block_row_sum<T, CS>(b, M, col_face, s0, s1, v, g, G, rr);
   group_reduce(red, b, G, g, rr, sum);
   if (mode == 0) {
-    if (threadIdx.x < b) y[o + threadIdx.x] = base[o + threadIdx.x] - red[G * b + threadIdx.x];
+    if (threadIdx.x < b) y[o + threadIdx.x] = base - red[G * b + threadIdx.x];
     return;
   }
   // s = base_i - sum  ->  svec; then y_i = Uinv s
   __shared__ double svec[128];
-  if (threadIdx.x < b) svec[threadIdx.x] = base[o + threadIdx.x] - red[G * b + threadIdx.x];
+  if (threadIdx.x < b) svec[threadIdx.x] = base - red[G * b + threadIdx.x];
   __syncthreads();
   double acc = 0.0;
   if (g < G) {
-    const T* blk = M + (size_t)ds * b * b + rr;
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    int cc = g;
+#pragma unroll
+    for (int u = 0; u < NI; ++u)
+      if (g + u * G < b) a[u & 3] += (double)inv[u] * svec[g + u * G];
+    int cc = g + NI * G;
     for (; cc + 3 * G < b; cc += 4 * G) {
       T m[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) m[u] = blk[(size_t)(cc + u * G) * b];
+      for (int u = 0; u < 4; ++u) m[u] = dblk[(size_t)(cc + u * G) * b];
 #pragma unroll
       for (int u = 0; u < 4; ++u) a[u] += (double)m[u] * svec[cc + u * G];
     }
-    for (; cc < b; cc += G) a[0] += (double)blk[(size_t)cc * b] * svec[cc];
+    for (; cc < b; cc += G) a[0] += (double)dblk[(size_t)cc * b] * svec[cc];
     acc = (a[0] + a[1]) + (a[2] + a[3]);
   }
   group_reduce(red, b, G, g, rr, acc);
@@ -525,14 +564,23 @@ using namespace iedg;
 
 namespace iedg {
 
+template <typename T>
+static void spmv_run(iedg_mesh m, const void* K, const double* x, const double* rhs, double* y, int mode,
+                     hipStream_t stream, const int* skip) {
+#define IEDG_SPMV(CS, THR)                                                                                       \
+  hipLaunchKernelGGL((spmv_kernel<T, CS, THR>), dim3(m->n_face), dim3(THR), 0, stream, m->b, m->d_row_face,      \
+                     m->d_row_ptr, m->d_col_face, (const T*)K, x, rhs, y, mode, skip)
+  // (blocks up to 8 wide are one unit each in any case)
+  if (m->b <= 8) IEDG_SPMV(8, PTHR);
+  else if (m->n_face < kManyRows) IEDG_SPMV(16, PTHR);
+  else IEDG_SPMV(0, STHR);
+#undef IEDG_SPMV
+}
+
 iedg_status spmv_launch(iedg_context ctx, iedg_mesh m, iedg_prec kprec, const void* K, const double* x,
                         const double* rhs, double* y, int mode, hipStream_t stream, const int* skip) {
-  if (kprec == IEDG_F64)
-    hipLaunchKernelGGL(spmv_kernel<double>, dim3(m->n_face), dim3(STHR), 0, stream, m->b, m->d_row_face,
-                       m->d_row_ptr, m->d_col_face, (const double*)K, x, rhs, y, mode, skip);
-  else
-    hipLaunchKernelGGL(spmv_kernel<float>, dim3(m->n_face), dim3(STHR), 0, stream, m->b, m->d_row_face,
-                       m->d_row_ptr, m->d_col_face, (const float*)K, x, rhs, y, mode, skip);
+  if (kprec == IEDG_F64) spmv_run<double>(m, K, x, rhs, y, mode, stream, skip);
+  else spmv_run<float>(m, K, x, rhs, y, mode, stream, skip);
   IEDG_LAUNCH_CHECK(ctx, "spmv launch");
   return IEDG_OK;
 }
@@ -547,8 +595,13 @@ template <typename T>
 static void sweep_launch(iedg_mesh m, int l0, int l1, int n_copy, const T* M, const double* x, double* y,
                          const double* v, int mode, hipStream_t stream, const int* skip) {
   const int r0 = m->level_ptr[l0], cnt = m->level_ptr[l1] - r0;
-  hipLaunchKernelGGL(sweep_kernel<T>, dim3(cnt), dim3(STHR), 0, stream, m->b, m->d_level_rows + r0,
-                     m->d_row_face, m->d_row_ptr, m->d_diag_slot, m->d_col_face, M, x, y, v, mode, n_copy, skip);
+#define IEDG_SWEEP(CS, THR)                                                                                     \
+  hipLaunchKernelGGL((sweep_kernel<T, CS, THR>), dim3(cnt), dim3(THR), 0, stream, m->b, m->d_level_desc + r0,   \
+                     m->d_col_face, M, x, y, v, mode, n_copy, skip)
+  if (m->b <= 8) IEDG_SWEEP(8, PTHR);
+  else if (cnt < kManyRows) IEDG_SWEEP(16, PTHR);
+  else IEDG_SWEEP(0, STHR);
+#undef IEDG_SWEEP
 }
 
 template <typename T>
@@ -739,78 +792,113 @@ __global__ __launch_bounds__(256) void ilu0_small_kernel(int nrows, const int32_
   if (!ok) latch_status(status, IEDG_ERR_SINGULAR, i);
 }
 
-// The same factorisation with the row's blocks staged in LDS: one wave per
-// block row (one row a workgroup).  Every slot of row i (A_ik, the updated
-// A_ij, the pivot block) lives in LDS from the first read to the final
-// write-back, so the chain of lower slots runs without the global stores,
-// waits and cache invalidations between slots; only U_kk^{-1} and U_kj
-// (rows of earlier levels) come from global memory, one slot ahead as in
-// ilu0_small_kernel.  The arithmetic is that kernel's, operation for
-// operation.  Dynamic LDS: the longest row of the level, in blocks.
+// The same factorisation with the row's blocks staged in LDS, one workgroup
+// per block row.  Every slot of row i (A_ik, the updated A_ij, the pivot block)
+// lives in LDS from the first read to the final write-back; only U_kk^{-1} and
+// U_kj (rows of earlier levels) come from global memory.  What bounds it is
+// the chain of lower slots, so each step of the chain is spread thin: B*B
+// lanes form one entry of L_ik each, then the threads take one column of one
+// updated block each (SUNITS of them with their operands fetched a slot ahead
+// and the indices of those two slots ahead).  The entries' sums are those of
+// ilu0_small_kernel, operation for operation.  One wave a row, a whole block a
+// lane, took 128 us a level at b = 5 (rows of some 150 blocks, FP64).
+// Dynamic LDS: the longest row of the level, in blocks, and its slot lists.
+constexpr int SFTHR = 256, SUNITS = 2;
+
 template <typename T, int B>
-__global__ __launch_bounds__(64) void ilu0_small_lds_kernel(const int32_t* __restrict__ rows,
-                                                            const int32_t* __restrict__ row_ptr,
-                                                            const int32_t* __restrict__ diag_slot,
-                                                            const int32_t* __restrict__ lptr,
-                                                            const int32_t* __restrict__ lslot,
-                                                            const int32_t* __restrict__ uptr,
-                                                            const int32_t* __restrict__ upd, T* M,
-                                                            DeviceStatus* status) {
+__global__ __launch_bounds__(SFTHR) void ilu0_small_lds_kernel(const int32_t* __restrict__ rows,
+                                                               const int32_t* __restrict__ row_ptr,
+                                                               const int32_t* __restrict__ diag_slot,
+                                                               const int32_t* __restrict__ lptr,
+                                                               const int32_t* __restrict__ lslot,
+                                                               const int32_t* __restrict__ uptr,
+                                                               const int2* __restrict__ upd, T* M,
+                                                               DeviceStatus* status) {
   constexpr int BB = B * B;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   T* R = reinterpret_cast<T*>(lds_raw);
   const int lane = threadIdx.x;
   const int i = rows[blockIdx.x];
-  const int s0 = row_ptr[i], nv = (row_ptr[i + 1] - s0) * BB;
+  const int s0 = row_ptr[i], len = row_ptr[i + 1] - s0, nv = len * BB;
+  const int l0 = lptr[i], nl = lptr[i + 1] - l0;
+  int* up = reinterpret_cast<int*>(R + nv);  // nl + 1: first update of each lower slot
+  int* sl = up + nl + 1;                     // nl x 2: slot (i,k), diagonal slot of k
   const T* Mrow = M + (size_t)s0 * BB;
-  for (int q = lane; q < nv; q += 64) R[q] = Mrow[q];
-  const int l0 = lptr[i], l1 = lptr[i + 1];
-  T un[BB], ukn[BB];
-  if (l0 < l1) {
-    small_load<T, B>(M + (size_t)lslot[2 * l0 + 1] * BB, un);
-    const int x0 = uptr[l0] + lane;
-    if (x0 < uptr[l0 + 1]) small_load<T, B>(M + (size_t)upd[2 * x0] * BB, ukn);
-  }
+  for (int q = lane; q < nv; q += SFTHR) R[q] = Mrow[q];
+  for (int q = lane; q <= nl; q += SFTHR) up[q] = uptr[l0 + q];
+  for (int q = lane; q < 2 * nl; q += SFTHR) sl[q] = lslot[2 * l0 + q];
   __syncthreads();
-  for (int l = l0; l < l1; ++l) {
-    const int sik = lslot[2 * l] - s0;
-    const int xb = uptr[l], xe = uptr[l + 1];
-    T a[BB], u[BB], L[BB], uk0[BB], c0[BB];
-    small_load<T, B>(R + sik * BB, a);
-    if (xb + lane < xe) small_load<T, B>(R + (upd[2 * (xb + lane) + 1] - s0) * BB, c0);
+  // unit w of slot l: column w % B of its update w / B
+  auto fetch_ids = [&](int l, int2 (&id)[SUNITS]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < BB; ++q) {
-      u[q] = un[q];
-      uk0[q] = ukn[q];
+    for (int r = 0; r < SUNITS; ++r) {
+      const int x = l < nl ? up[l] + (lane + r * SFTHR) / B : 0;
+      id[r] = l < nl && x < up[l + 1] ? upd[x] : make_int2(-1, 0);
     }
-    if (l + 1 < l1) {
-      small_load<T, B>(M + (size_t)lslot[2 * (l + 1) + 1] * BB, un);
-      const int x1 = xe + lane;
-      if (x1 < uptr[l + 2]) small_load<T, B>(M + (size_t)upd[2 * x1] * BB, ukn);
-    }
-    small_mm<T, B, false>(a, u, L);
-    if (xb + lane < xe) {
-      small_mm<T, B, true>(L, uk0, c0);
-      T* C = R + (upd[2 * (xb + lane) + 1] - s0) * BB;
+  };
+  auto fetch = [&](int l, const int2 (&id)[SUNITS], T (&uk)[SUNITS][B], T (&u)[B]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int q = 0; q < BB; ++q) C[q] = c0[q];
-    }
-    for (int x = xb + lane + 64; x < xe; x += 64) {
-      T* C = R + (upd[2 * x + 1] - s0) * BB;
-      T ukj[BB], c[BB];
-      small_load<T, B>(M + (size_t)upd[2 * x] * BB, ukj);
-      small_load<T, B>(C, c);
-      small_mm<T, B, true>(L, ukj, c);
+    for (int r = 0; r < SUNITS; ++r)
+      if (id[r].x >= 0) {
+        const T* p = M + (size_t)id[r].x * BB + (lane + r * SFTHR) % B * B;
 #pragma unroll
-      for (int q = 0; q < BB; ++q) C[q] = c[q];
+        for (int k = 0; k < B; ++k) uk[r][k] = p[k];
+      }
+    if (l < nl && lane < BB) {
+      const T* p = M + (size_t)sl[2 * l + 1] * BB + lane / B * B;
+#pragma unroll
+      for (int k = 0; k < B; ++k) u[k] = p[k];
     }
-    // every lane has read A_ik (into a) before lane 0 replaces it by L_ik;
-    // the updates of this slot are visible before the next slot reads
+  };
+  // C -= L U_kj, one column
+  auto update = [&](const T* Lk, const T (&uk)[B], T* C) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < B; ++r) {
+      T v = T(0);
+#pragma unroll
+      for (int k = 0; k < B; ++k) v += Lk[k * B + r] * uk[k];
+      C[r] -= v;
+    }
+  };
+  int2 id[SUNITS], idn[SUNITS];
+  T uk[SUNITS][B], ukn[SUNITS][B], u[B], un[B];
+  fetch_ids(0, id);
+  fetch(0, id, uk, u);
+  fetch_ids(1, idn);
+  for (int l = 0; l < nl; ++l) {
+    int dst[SUNITS];
+#pragma unroll
+    for (int r = 0; r < SUNITS; ++r) dst[r] = id[r].x >= 0 ? id[r].y - s0 : -1;
+    fetch(l + 1, idn, ukn, un);
+#pragma unroll
+    for (int r = 0; r < SUNITS; ++r) id[r] = idn[r];
+    fetch_ids(l + 2, idn);
+    T* Lk = R + sl[2 * l] * BB - s0 * BB;
+    if (lane < BB) {  // (one wave: every entry of A_ik is read before L_ik replaces it)
+      T v = T(0);
+#pragma unroll
+      for (int k = 0; k < B; ++k) v += Lk[k * B + lane % B] * u[k];
+      Lk[lane] = v;
+    }
     __syncthreads();
-    if (lane == 0)
 #pragma unroll
-      for (int q = 0; q < BB; ++q) R[sik * BB + q] = L[q];
+    for (int r = 0; r < SUNITS; ++r)
+      if (dst[r] >= 0) update(Lk, uk[r], R + dst[r] * BB + (lane + r * SFTHR) % B * B);
+    for (int w = lane + SUNITS * SFTHR; w < (up[l + 1] - up[l]) * B; w += SFTHR) {
+      const int2 e = upd[up[l] + w / B];
+      const T* p = M + (size_t)e.x * BB + w % B * B;
+      T uw[B];
+#pragma unroll
+      for (int k = 0; k < B; ++k) uw[k] = p[k];
+      update(Lk, uw, R + (e.y - s0) * BB + w % B * B);
+    }
     __syncthreads();
+#pragma unroll
+    for (int r = 0; r < SUNITS; ++r)
+#pragma unroll
+      for (int k = 0; k < B; ++k) uk[r][k] = ukn[r][k];
+#pragma unroll
+    for (int k = 0; k < B; ++k) u[k] = un[k];
   }
   if (lane == 0) {
     T* Dg = R + (diag_slot[i] - s0) * BB;
@@ -872,7 +960,7 @@ __global__ __launch_bounds__(64) void ilu0_small_lds_kernel(const int32_t* __res
   }
   __syncthreads();
   T* Mw = M + (size_t)s0 * BB;
-  for (int q = lane; q < nv; q += 64) Mw[q] = R[q];
+  for (int q = lane; q < nv; q += SFTHR) Mw[q] = R[q];
 }
 
 // LDS a workgroup of ilu0_small_lds_kernel may take (the rest of the CU's
@@ -895,10 +983,11 @@ static iedg_status factor_levels_small(iedg_context ctx, iedg_mesh m, T* M, hipS
       const int i = m->level_rows[r];
       len = std::max(len, m->row_ptr[i + 1] - m->row_ptr[i]);
     }
-    const size_t lds = blk * (size_t)len;
+    const size_t lds = blk * (size_t)len + sizeof(int) * (3 * (size_t)len + 1);
     if (lds <= kSmallRowLds) {
-      hipLaunchKernelGGL(kern_lds, dim3(cnt), dim3(64), lds, stream, m->d_level_rows + r0, m->d_row_ptr,
-                         m->d_diag_slot, m->d_ilu_lptr, m->d_ilu_l, m->d_ilu_uptr, m->d_ilu_upd, M, ctx->d_status);
+      hipLaunchKernelGGL(kern_lds, dim3(cnt), dim3(SFTHR), lds, stream, m->d_level_rows + r0, m->d_row_ptr,
+                         m->d_diag_slot, m->d_ilu_lptr, m->d_ilu_l, m->d_ilu_uptr,
+                         reinterpret_cast<const int2*>(m->d_ilu_upd), M, ctx->d_status);
     } else {
       hipLaunchKernelGGL(kern, dim3((cnt + 3) / 4), dim3(256), 0, stream, cnt,
                          m->d_level_rows + r0, m->d_diag_slot, m->d_ilu_lptr, m->d_ilu_l, m->d_ilu_uptr,
