@@ -129,6 +129,20 @@ __device__ inline void wave_dot_rows(const T* const (&rows)[R], const double* ve
   for (int r = 0; r < R; ++r) out[r] = wave_sum(s[r]);
 }
 
+// Value of lane l (uniform) of a double.
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// Threads of the kernels that solve with one element's factors per workgroup:
+// 1024 while there are few elements, whose time is then the chain of row
+// blocks and grows with the loads a wave has to take in turn (256 elements of
+// n = 1280, FP32: 873 us with 256 threads), 256 where several workgroups share
+// every CU and HBM bounds them (2,048 such elements: 4.8 TB/s).
+constexpr int kElementWide = 1024, kElementNarrow = 256;
+inline bool element_wide(int n_elem) { return n_elem <= 512; }
+
 // Device status word: the smallest failing index (element or block row)
 // and its code in one 64-bit word, (index << 8) | -code, all ones when
 // clear, so that one atomicMin keeps an index with its own code whatever

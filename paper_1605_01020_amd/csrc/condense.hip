@@ -12,16 +12,15 @@ namespace iedg {
 // ---- right-hand side condensation: w = L^{-1} P F, r = -L21 w ----------
 // Position i of P A is physical row perm[i] of LU and of w.  Rows are taken
 // four per wave at a time (wave_dot_rows, 16 loads in flight per lane);
-// 64-row diagonal blocks of L are staged in LDS in the storage precision and
-// solved by one wave.  LDS stays small so that several elements share a CU.
-constexpr int RTHR = 256;
-
-template <typename T>
-__global__ __launch_bounds__(RTHR) void condense_rhs_kernel(int n, int t, const T* LU, const int32_t* perm,
-                                                            const T* L21, const double* F, double* w,
-                                                            double* r) {
+// 64-row diagonal blocks of L (fetched ahead of the block's row sums by 1,024
+// threads) are staged in LDS in the storage precision and solved by one wave, a lane read
+// and a fused multiply-add a step.
+template <typename T, int THR>
+__global__ __launch_bounds__(THR) void condense_rhs_kernel(int n, int t, const T* LU, const int32_t* perm,
+                                                           const T* L21, const double* F, double* w,
+                                                           double* r) {
   const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  constexpr int RW = RTHR / 64;
+  constexpr int RW = THR / 64, BV = 64 * 64 / THR;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* y = reinterpret_cast<double*>(smem_raw);      // n
   int* sp = reinterpret_cast<int*>(y + n);              // n
@@ -29,13 +28,24 @@ __global__ __launch_bounds__(RTHR) void condense_rhs_kernel(int n, int t, const 
   const T* L = LU + (size_t)e * n * n;
   const int32_t* p = perm + (size_t)e * n;
   const double* f = F + (size_t)e * n;
-  for (int i = tid; i < n; i += RTHR) {
+  for (int i = tid; i < n; i += THR) {
     sp[i] = p[i];
     y[i] = f[p[i]];
   }
   __syncthreads();
   for (int i0 = 0; i0 < n; i0 += 64) {
     const int i1 = min(i0 + 64, n), bw = i1 - i0;
+    // (256 threads would hold 16 values each, and occupancy matters there)
+    constexpr bool AHEAD = BV <= 4;
+    auto diagonal = [&](int q) __attribute__((always_inline)) -> T {
+      const int rr = q / 64, cc = q % 64;
+      return (rr < bw && cc < rr) ? L[(size_t)sp[i0 + rr] * n + i0 + cc] : T(0);
+    };
+    T d[AHEAD ? BV : 1];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int v = 0; v < BV; ++v) d[v] = diagonal(tid + v * THR);
+    }
     if (i0 > 0) {
       for (int i = i0 + 4 * wv; i < i1; i += 4 * RW) {
         const T* rows[4];
@@ -51,22 +61,28 @@ __global__ __launch_bounds__(RTHR) void condense_rhs_kernel(int n, int t, const 
         }
       }
     }
-    for (int q = tid; q < 64 * 64; q += RTHR) {
-      const int rr = q / 64, cc = q % 64;
-      blk[rr * 65 + cc] = (rr < bw && cc < rr) ? L[(size_t)sp[i0 + rr] * n + i0 + cc] : T(0);
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int v = 0; v < BV; ++v) {
+        const int q = tid + v * THR;
+        blk[q / 64 * 65 + q % 64] = d[v];
+      }
+    } else {
+      for (int q = tid; q < 64 * 64; q += THR) blk[q / 64 * 65 + q % 64] = diagonal(q);
     }
     __syncthreads();
     if (wv == 0) {
       double yl = lane < bw ? y[i0 + lane] : 0.0;
+#pragma unroll 4
       for (int k = 0; k < bw; ++k) {
-        const double yk = __shfl(yl, k, kWave);
-        if (lane > k) yl -= (double)blk[lane * 65 + k] * yk;
+        const double l = (double)blk[lane * 65 + k], yk = lane_value(yl, k);
+        yl = lane > k ? fma(-l, yk, yl) : yl;
       }
       if (lane < bw) y[i0 + lane] = yl;
     }
     __syncthreads();
   }
-  for (int i = tid; i < n; i += RTHR) w[(size_t)e * n + sp[i]] = y[i];
+  for (int i = tid; i < n; i += THR) w[(size_t)e * n + sp[i]] = y[i];
   const T* L2 = L21 + (size_t)e * t * n;
   for (int i = 4 * wv; i < t; i += 4 * RW) {
     const T* rows[4];
@@ -170,20 +186,21 @@ extern "C" iedg_status iedg_condense_rhs(iedg_context ctx, int32_t n_elem, int32
   if (n_elem == 0) return IEDG_OK;
   if (!LU || !perm || !L21 || !F || !w || !r) return set_error(ctx, IEDG_ERR_INVALID_ARG, "condense_rhs: null pointer");
   const size_t smem0 = sizeof(double) * n_local + sizeof(int) * ((n_local + 3) & ~3);
-  if (prec == IEDG_F64) {
-    const size_t smem = smem0 + sizeof(double) * 64 * 65;
-    auto k = condense_rhs_kernel<double>;
-    IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-    hipLaunchKernelGGL(k, dim3(n_elem), dim3(RTHR), smem, stream, n_local, n_trace_elem, (const double*)LU, perm,
-                       (const double*)L21, F, w, r);
-  } else if (prec == IEDG_F32 || prec == IEDG_BF16) {
-    const size_t smem = smem0 + sizeof(float) * 64 * 65;
-    auto k = condense_rhs_kernel<float>;
-    IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-    hipLaunchKernelGGL(k, dim3(n_elem), dim3(RTHR), smem, stream, n_local, n_trace_elem, (const float*)LU, perm,
-                       (const float*)L21, F, w, r);
-  } else {
+  if (prec != IEDG_F64 && prec != IEDG_F32 && prec != IEDG_BF16)
     return set_error(ctx, IEDG_ERR_UNSUPPORTED, "condense_rhs: precision");
+  const bool f64 = prec == IEDG_F64, wide = element_wide(n_elem);
+  const size_t smem = smem0 + (f64 ? sizeof(double) : sizeof(float)) * 64 * 65;
+  const dim3 thr(wide ? kElementWide : kElementNarrow);
+  if (f64) {
+    auto k = wide ? condense_rhs_kernel<double, kElementWide> : condense_rhs_kernel<double, kElementNarrow>;
+    IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    hipLaunchKernelGGL(k, dim3(n_elem), thr, smem, stream, n_local, n_trace_elem, (const double*)LU, perm,
+                       (const double*)L21, F, w, r);
+  } else {
+    auto k = wide ? condense_rhs_kernel<float, kElementWide> : condense_rhs_kernel<float, kElementNarrow>;
+    IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    hipLaunchKernelGGL(k, dim3(n_elem), thr, smem, stream, n_local, n_trace_elem, (const float*)LU, perm,
+                       (const float*)L21, F, w, r);
   }
   IEDG_LAUNCH_CHECK(ctx, "condense_rhs launch");
   return IEDG_OK;

@@ -10,30 +10,32 @@ namespace iedg {
 constexpr int LTHR = 256;
 constexpr int LWAVES = LTHR / 64;
 
-// z_e = U^{-1} (w_e - U12_e uhat_e): one workgroup per element.  Position i
-// of the factorisation lives in physical row perm[i] of LU, U12 and w.
-// Rows are processed four per wave at a time (wave_dot_rows) so each lane
-// keeps 16 loads in flight; 64-row diagonal blocks of U are staged in LDS in
-// the storage precision and solved by one wave.  LDS stays small so that
-// several elements share a CU.
-template <typename T>
-__global__ __launch_bounds__(LTHR) void backsolve_kernel(int n, int t, int b, int S, const int32_t* elem_faces, const T* LU,
-                                                         const int32_t* perm, const T* U12, const double* w,
-                                                         const double* uhat, double* z) {
+// z_e = U^{-1} (w_e - U12_e uhat_e): one workgroup of THR threads per element.
+// Position i of the factorisation lives in physical row perm[i] of LU, U12 and
+// w.  Rows are processed four per wave at a time (wave_dot_rows) so each lane
+// keeps 16 loads in flight; 64-row diagonal blocks of U (fetched ahead of the
+// block's row sums by 1,024 threads) are staged in LDS in the storage precision and solved by
+// one wave.  A step of that solve is a lane read and four fused multiply-adds:
+// the quotient by the pivot is its reciprocal's product, corrected once.
+template <typename T, int THR>
+__global__ __launch_bounds__(THR) void backsolve_kernel(int n, int t, int b, int S, const int32_t* elem_faces, const T* LU,
+                                                        const int32_t* perm, const T* U12, const double* w,
+                                                        const double* uhat, double* z) {
+  constexpr int WAVES = THR / 64, BV = 64 * 64 / THR;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* ue = reinterpret_cast<double*>(smem_raw);  // t
   double* y = ue + t;                                // n
   int* sp = reinterpret_cast<int*>(y + n);           // n
   T* blk = reinterpret_cast<T*>(sp + ((n + 3) & ~3));  // 64 x 65
   const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int i = tid; i < t; i += LTHR) {
+  for (int i = tid; i < t; i += THR) {
     const int a = i / b, l = i % b;
     ue[i] = uhat[(size_t)elem_faces[S * e + a] * b + l];
   }
-  for (int i = tid; i < n; i += LTHR) sp[i] = perm[(size_t)e * n + i];
+  for (int i = tid; i < n; i += THR) sp[i] = perm[(size_t)e * n + i];
   __syncthreads();
   const T* U12e = U12 + (size_t)e * n * t;
-  for (int i = 4 * wv; i < n; i += 4 * LWAVES) {
+  for (int i = 4 * wv; i < n; i += 4 * WAVES) {
     const T* rows[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) rows[r] = U12e + (size_t)sp[min(i + r, n - 1)] * t;
@@ -51,9 +53,20 @@ __global__ __launch_bounds__(LTHR) void backsolve_kernel(int n, int t, int b, in
   const int nblk = (n + 63) / 64;
   for (int bi = nblk - 1; bi >= 0; --bi) {
     const int i0 = bi * 64, i1 = min(i0 + 64, n), bw = i1 - i0;
+    // (256 threads would hold 16 values each, and occupancy matters there)
+    constexpr bool AHEAD = BV <= 4;
+    auto diagonal = [&](int q) __attribute__((always_inline)) -> T {
+      const int rr = q / 64, cc = q % 64;
+      return (rr < bw && cc < bw && cc >= rr) ? U[(size_t)sp[i0 + rr] * n + i0 + cc] : T(0);
+    };
+    T d[AHEAD ? BV : 1];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int v = 0; v < BV; ++v) d[v] = diagonal(tid + v * THR);
+    }
     // y[i0:i1] -= U[i0:i1, i1:n] z[i1:n]   (z stored in y beyond i1)
     if (i1 < n) {
-      for (int i = i0 + 4 * wv; i < i1; i += 4 * LWAVES) {
+      for (int i = i0 + 4 * wv; i < i1; i += 4 * WAVES) {
         const T* rows[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) rows[r] = U + (size_t)sp[min(i + r, i1 - 1)] * n + i1;
@@ -67,23 +80,32 @@ __global__ __launch_bounds__(LTHR) void backsolve_kernel(int n, int t, int b, in
         }
       }
     }
-    for (int q = tid; q < 64 * 64; q += LTHR) {
-      const int rr = q / 64, cc = q % 64;
-      blk[rr * 65 + cc] = (rr < bw && cc < bw && cc >= rr) ? U[(size_t)sp[i0 + rr] * n + i0 + cc] : T(0);
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int v = 0; v < BV; ++v) {
+        const int q = tid + v * THR;
+        blk[q / 64 * 65 + q % 64] = d[v];
+      }
+    } else {
+      for (int q = tid; q < 64 * 64; q += THR) blk[q / 64 * 65 + q % 64] = diagonal(q);
     }
     __syncthreads();
     if (wv == 0) {
       double yl = lane < bw ? y[i0 + lane] : 0.0;
+      const double dg = lane < bw ? (double)blk[lane * 65 + lane] : 1.0, rd = 1.0 / dg;
+#pragma unroll 4
       for (int k = bw - 1; k >= 0; --k) {
-        const double zk = __shfl(yl, k, kWave) / (double)blk[k * 65 + k];
-        if (lane == k) yl = zk;
-        if (lane < k) yl -= (double)blk[lane * 65 + k] * zk;
+        const double u = (double)blk[lane * 65 + k];
+        double zl = yl * rd;  // meant for lane k alone
+        zl = fma(fma(-zl, dg, yl), rd, zl);
+        const double zk = lane_value(zl, k);
+        yl = lane == k ? zk : lane < k ? fma(-u, zk, yl) : yl;
       }
       if (lane < bw) y[i0 + lane] = yl;
     }
     __syncthreads();
   }
-  for (int i = tid; i < n; i += LTHR) z[(size_t)e * n + i] = y[i];
+  for (int i = tid; i < n; i += THR) z[(size_t)e * n + i] = y[i];
 }
 
 // Rows of rF_e = F_e - A_e z_e - B_e u_e and of q_e = C_e z_e + D_e u_e: a
@@ -208,17 +230,18 @@ extern "C" iedg_status iedg_backsolve_local(iedg_context ctx, iedg_mesh mesh, in
   if (!ctx || !mesh || !LU || !perm || !U12 || !w || !uhat || !z || n_local <= 0) return IEDG_ERR_INVALID_ARG;
   const int n = n_local, t = mesh->t, b = mesh->b;
   const size_t smem_ints = sizeof(double) * (t + n) + sizeof(int) * ((n + 3) & ~3);
-  if (prec == IEDG_F64) {
-    const size_t smem = smem_ints + sizeof(double) * 64 * 65;
-    auto k = backsolve_kernel<double>;
+  const bool f64 = prec == IEDG_F64, wide = element_wide(mesh->n_elem);
+  const size_t smem = smem_ints + (f64 ? sizeof(double) : sizeof(float)) * 64 * 65;
+  const dim3 thr(wide ? kElementWide : kElementNarrow);
+  if (f64) {
+    auto k = wide ? backsolve_kernel<double, kElementWide> : backsolve_kernel<double, kElementNarrow>;
     IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-    hipLaunchKernelGGL(k, dim3(mesh->n_elem), dim3(LTHR), smem, stream, n, t, b, mesh->slots, mesh->d_elem_faces,
+    hipLaunchKernelGGL(k, dim3(mesh->n_elem), thr, smem, stream, n, t, b, mesh->slots, mesh->d_elem_faces,
                        (const double*)LU, perm, (const double*)U12, w, uhat, z);
   } else {
-    const size_t smem = smem_ints + sizeof(float) * 64 * 65;
-    auto k = backsolve_kernel<float>;
+    auto k = wide ? backsolve_kernel<float, kElementWide> : backsolve_kernel<float, kElementNarrow>;
     IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-    hipLaunchKernelGGL(k, dim3(mesh->n_elem), dim3(LTHR), smem, stream, n, t, b, mesh->slots, mesh->d_elem_faces,
+    hipLaunchKernelGGL(k, dim3(mesh->n_elem), thr, smem, stream, n, t, b, mesh->slots, mesh->d_elem_faces,
                        (const float*)LU, perm, (const float*)U12, w, uhat, z);
   }
   IEDG_LAUNCH_CHECK(ctx, "backsolve launch");
