@@ -22,11 +22,61 @@ constexpr int KPER = 8;                 // values per thread per chunk
 constexpr int KCH = KTHR * KPER;        // chunk length per workgroup
 constexpr int MAXV = 256;               // max Krylov vectors per cycle + 2
 
+// The Gram-Schmidt kernels take KVEC basis vectors at a time: their loads are
+// in flight together and one pair of barriers reduces their sums, so a pass
+// over few unknowns costs a memory round trip for KVEC vectors instead of one
+// each (N = 10,800, up to 12 vectors: 8.6 us one by one).
+constexpr int KVEC = 4;
+
+// Sums over the workgroup of KVEC values each (order as in block_sum); valid
+// for thread q < KVEC as its own sum.
+__device__ inline double block_sums(const double (&v)[KVEC], double (&red)[KVEC][KTHR / 64]) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  double s[KVEC];
+#pragma unroll
+  for (int q = 0; q < KVEC; ++q) s[q] = wave_sum(v[q]);
+  __syncthreads();
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < KVEC; ++q) red[q][wid] = s[q];
+  __syncthreads();
+  double r = 0.0;
+  if (threadIdx.x < KVEC)
+    for (int i = 0; i < KTHR / 64; ++i) r += red[threadIdx.x][i];
+  return r;
+}
+
+// partial[c * ld + k] = sum over chunk c of V_k . w, k < nv (w in registers).
+__device__ inline void chunk_dots(const double* V, int64_t ldv, int nv, const double (&wv)[KPER], int64_t base, int64_t N,
+                                  double* partial, double (&red)[KVEC][KTHR / 64]) {
+  for (int k0 = 0; k0 < nv; k0 += KVEC) {
+    double v[KVEC][KPER];
+#pragma unroll
+    for (int u = 0; u < KVEC; ++u) {
+      const double* vk = V + (int64_t)min(k0 + u, nv - 1) * ldv;
+#pragma unroll
+      for (int q = 0; q < KPER; ++q) {
+        const int64_t i = base + threadIdx.x + (int64_t)q * KTHR;
+        v[u][q] = i < N ? vk[i] : 0.0;
+      }
+    }
+    double s[KVEC];
+#pragma unroll
+    for (int u = 0; u < KVEC; ++u) {
+      s[u] = 0.0;
+#pragma unroll
+      for (int q = 0; q < KPER; ++q) s[u] += v[u][q] * wv[q];
+    }
+    const double r = block_sums(s, red);
+    if (threadIdx.x < KVEC && k0 + (int)threadIdx.x < nv) partial[k0 + threadIdx.x] = r;
+  }
+}
+
 // partial[c * ld + k] = sum over chunk c of V_k . w   (k < nv), and, when
 // self >= 0, partial[c * ld + self] = w . w
 __global__ __launch_bounds__(KTHR) void dots_kernel(const double* V, int64_t ldv, int nv, const double* w,
                                                     int64_t N, double* partial, int ld, int self, const int* skip) {
-  __shared__ double red[KTHR / 64];
+  __shared__ double red[KVEC][KTHR / 64];
   if (skip && *skip) return;
   const int c = blockIdx.x;
   const int64_t base = (int64_t)c * KCH;
@@ -36,22 +86,12 @@ __global__ __launch_bounds__(KTHR) void dots_kernel(const double* V, int64_t ldv
     const int64_t i = base + threadIdx.x + (int64_t)q * KTHR;
     wv[q] = i < N ? w[i] : 0.0;
   }
-  for (int k = 0; k < nv; ++k) {
-    const double* v = V + (int64_t)k * ldv;
-    double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < KPER; ++q) {
-      const int64_t i = base + threadIdx.x + (int64_t)q * KTHR;
-      if (i < N) s += v[i] * wv[q];
-    }
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) partial[(int64_t)c * ld + k] = s;
-  }
+  chunk_dots(V, ldv, nv, wv, base, N, partial + (int64_t)c * ld, red);
   if (self >= 0) {
     double s = 0.0;
 #pragma unroll
     for (int q = 0; q < KPER; ++q) s += wv[q] * wv[q];
-    s = block_sum(s, red);
+    s = block_sum(s, red[0]);
     if (threadIdx.x == 0) partial[(int64_t)c * ld + self] = s;
   }
 }
@@ -66,17 +106,9 @@ __global__ __launch_bounds__(KTHR) void cgs_update_kernel(const double* V, int64
                                                           double* hcol, int accumulate, double* partial_out,
                                                           int ld_out, int next_dots, const int* skip) {
   __shared__ double h[MAXV];
-  __shared__ double red[KTHR / 64];
+  __shared__ double red[KVEC][KTHR / 64];
   if (skip && *skip) return;
   const int c = blockIdx.x;
-  for (int k = threadIdx.x; k < nv; k += KTHR) {
-    double s = 0.0;
-    for (int q = 0; q < nb; ++q) s += partial_in[(int64_t)q * ld_in + k];
-    h[k] = s;
-  }
-  __syncthreads();
-  if (c == 0)
-    for (int k = threadIdx.x; k < nv; k += KTHR) hcol[k] = accumulate ? hcol[k] + h[k] : h[k];
   const int64_t base = (int64_t)c * KCH;
   double wv[KPER];
 #pragma unroll
@@ -84,13 +116,33 @@ __global__ __launch_bounds__(KTHR) void cgs_update_kernel(const double* V, int64
     const int64_t i = base + threadIdx.x + (int64_t)q * KTHR;
     wv[q] = i < N ? w[i] : 0.0;
   }
-  for (int k = 0; k < nv; ++k) {
-    const double* v = V + (int64_t)k * ldv;
-    const double hk = h[k];
+  // a wave per coefficient, the chunks dealt to its lanes
+  for (int k = threadIdx.x >> 6; k < nv; k += KTHR / 64) {
+    double s = 0.0;
+    for (int q = threadIdx.x & 63; q < nb; q += 64) s += partial_in[(int64_t)q * ld_in + k];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) h[k] = s;
+  }
+  __syncthreads();
+  if (c == 0)
+    for (int k = threadIdx.x; k < nv; k += KTHR) hcol[k] = accumulate ? hcol[k] + h[k] : h[k];
+  for (int k0 = 0; k0 < nv; k0 += KVEC) {
+    double v[KVEC][KPER];
 #pragma unroll
-    for (int q = 0; q < KPER; ++q) {
-      const int64_t i = base + threadIdx.x + (int64_t)q * KTHR;
-      if (i < N) wv[q] -= hk * v[i];
+    for (int u = 0; u < KVEC; ++u) {
+      const double* vk = V + (int64_t)min(k0 + u, nv - 1) * ldv;
+#pragma unroll
+      for (int q = 0; q < KPER; ++q) {
+        const int64_t i = base + threadIdx.x + (int64_t)q * KTHR;
+        v[u][q] = i < N ? vk[i] : 0.0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < KVEC; ++u) {
+      if (k0 + u >= nv) break;
+      const double hk = h[k0 + u];
+#pragma unroll
+      for (int q = 0; q < KPER; ++q) wv[q] -= hk * v[u][q];
     }
   }
 #pragma unroll
@@ -99,22 +151,12 @@ __global__ __launch_bounds__(KTHR) void cgs_update_kernel(const double* V, int64
     if (i < N) w[i] = wv[q];
   }
   if (next_dots) {
-    for (int k = 0; k < nv; ++k) {
-      const double* v = V + (int64_t)k * ldv;
-      double s = 0.0;
-#pragma unroll
-      for (int q = 0; q < KPER; ++q) {
-        const int64_t i = base + threadIdx.x + (int64_t)q * KTHR;
-        if (i < N) s += v[i] * wv[q];
-      }
-      s = block_sum(s, red);
-      if (threadIdx.x == 0) partial_out[(int64_t)c * ld_out + k] = s;
-    }
+    chunk_dots(V, ldv, nv, wv, base, N, partial_out + (int64_t)c * ld_out, red);
   } else {
     double s = 0.0;
 #pragma unroll
     for (int q = 0; q < KPER; ++q) s += wv[q] * wv[q];
-    s = block_sum(s, red);
+    s = block_sum(s, red[0]);
     if (threadIdx.x == 0) partial_out[(int64_t)c * ld_out] = s;
   }
 }
@@ -135,22 +177,23 @@ struct GmresScal {
   int pad;
 };
 
-// Reduce nb partial sums -> sqrt, fixed order (one thread).
+// Reduce nb partial sums -> sqrt, fixed order (by one wave, in every lane).
 __device__ inline double reduce_sqrt(const double* partial, int nb, int ld, int idx) {
   double s = 0.0;
-  for (int q = 0; q < nb; ++q) s += partial[(int64_t)q * ld + idx];
-  return sqrt(s);
+  for (int q = threadIdx.x; q < nb; q += 64) s += partial[(int64_t)q * ld + idx];
+  return sqrt(wave_sum(s));
 }
 
 // Finish Arnoldi step j: H[j+1, j] = ||w||, apply the stored rotations to
-// column j, form the new rotation and update g.  One thread.
+// column j, form the new rotation and update g.  One wave; its first lane
+// does all but the sums.
 __global__ void arnoldi_finish_kernel(const double* partial_norm, int nb, const double* partial_w0, int ld_w0,
                                       int idx_w0, double* H, int ldh, int j, double* cs, double* sn, double* g,
                                       GmresScal* sc, int device_control, int steps) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
   if (device_control && sc->done) return;
   const double hn = reduce_sqrt(partial_norm, nb, 1, 0);
   const double wn0 = reduce_sqrt(partial_w0, nb, ld_w0, idx_w0);
+  if (threadIdx.x != 0) return;
   double* hc = H + (int64_t)j * ldh;
   hc[j + 1] = hn;
   for (int i = 0; i < j; ++i) {
@@ -185,8 +228,8 @@ __global__ void arnoldi_finish_kernel(const double* partial_norm, int nb, const 
 // sc->norm = sqrt(sum of partials); sc->inv_scale = 1 / norm; optionally g = (norm, 0, ...)
 __global__ void norm_finish_kernel(const double* partial, int nb, int ld, int idx, GmresScal* sc, double* g,
                                    int m1) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
   const double nrm = reduce_sqrt(partial, nb, ld, idx);
+  if (threadIdx.x != 0) return;
   sc->norm = nrm;
   sc->inv_scale = nrm > 0.0 ? 1.0 / nrm : 0.0;
   if (g) {
