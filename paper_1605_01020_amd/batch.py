@@ -272,9 +272,19 @@ def _nnzb_estimate(hm):
 
 
 class BatchGroup:
-    """Meshes solved together: one persistent condensation launch over
-    every mesh of a precision (all element sizes), then every mesh's trace
-    solve; optionally captured in a graph."""
+    """Meshes solved together: the condensation of every mesh of a precision
+    (all element sizes), then every mesh's trace solve; optionally captured in
+    a graph.
+
+    The trace solves are chains of short launches that leave most of the chip
+    idle (a sweep level of a small mesh has some tens of rows), and they share
+    nothing: they run beside each other on BRANCHES streams, forked from the
+    caller's stream after the condensation and joined to it at the end, so
+    that every later use of the results on the caller's stream is ordered
+    after them.  Meshes that share a workspace stay on one branch."""
+
+    # the hardware queues a process has
+    BRANCHES = 4
 
     def __init__(self, ctx, sims):
         self.ctx, self.sims = ctx, sims
@@ -284,12 +294,43 @@ class BatchGroup:
         self.plans = [api.CondenseBatch(ctx, [s.condense_segment() for s in group], prec=prec)
                       for prec, group in sorted(by_prec.items())]
         self.graph = None
+        self.branches = self._branches()
+        self.streams = [torch.cuda.Stream() for _ in self.branches[1:]]
+
+    def _branches(self):
+        """The meshes dealt to branches, the longest solves first."""
+        shared = {}
+        for s in self.sims:
+            parts = [shared[k] for k in {id(g) for g in s.gm} | {id(s.mesh)} if k in shared]
+            part = parts[0] if parts else []
+            for q in parts[1:]:
+                if q is not part:
+                    part.extend(q)
+            part.append(s)
+            for x in part:
+                shared.update({k: part for k in [id(g) for g in x.gm] + [id(x.mesh)]})
+        work = {id(p): p for p in shared.values()}.values()
+        out = [[] for _ in range(min(self.BRANCHES, len(work)))]
+        load = [0] * len(out)
+        for part in sorted(work, key=lambda p: -sum(s.mesh.n_trace for s in p)):
+            k = load.index(min(load))
+            out[k] += part
+            load[k] += sum(s.mesh.n_trace for s in part)
+        return out
 
     def enqueue(self):
         for pl in self.plans:
             pl.run()
-        for s in self.sims:
+        here = torch.cuda.current_stream()
+        for st, sims in zip(self.streams, self.branches[1:]):
+            st.wait_stream(here)
+            with torch.cuda.stream(st):
+                for s in sims:
+                    s.enqueue_after_condense()
+        for s in self.branches[0] if self.branches else []:
             s.enqueue_after_condense()
+        for st in self.streams:
+            here.wait_stream(st)
 
     def capture(self):
         """Capture enqueue() in a graph (after an eager run has set up every
