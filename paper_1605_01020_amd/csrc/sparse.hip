@@ -598,7 +598,7 @@ static void sweep_launch(iedg_mesh m, int l0, int l1, int n_copy, const T* M, co
 #define IEDG_SWEEP(CS, THR)                                                                                     \
   hipLaunchKernelGGL((sweep_kernel<T, CS, THR>), dim3(cnt), dim3(THR), 0, stream, m->b, m->d_level_desc + r0,   \
                      m->d_col_face, M, x, y, v, mode, n_copy, skip)
-  if (m->b <= 8) IEDG_SWEEP(8, PTHR);
+  if (m->b <= 8) IEDG_SWEEP(8, STHR);
   else if (cnt < kManyRows) IEDG_SWEEP(16, PTHR);
   else IEDG_SWEEP(0, STHR);
 #undef IEDG_SWEEP
