@@ -800,10 +800,11 @@ __global__ __launch_bounds__(256) void ilu0_small_kernel(int nrows, const int32_
 // lanes form one entry of L_ik each, then the threads take one column of one
 // updated block each (SUNITS of them with their operands fetched a slot ahead
 // and the indices of those two slots ahead).  The entries' sums are those of
-// ilu0_small_kernel, operation for operation.  One wave a row, a whole block a
-// lane, took 128 us a level at b = 5 (rows of some 150 blocks, FP64).
+// ilu0_small_kernel, operation for operation.  A level at b = 5, FP64 (rows of
+// up to 206 blocks, some 40 rows): 128 us with one wave a row and a whole block
+// a lane, 72 us with 256 threads of two units, 48 us with 512 of one.
 // Dynamic LDS: the longest row of the level, in blocks, and its slot lists.
-constexpr int SFTHR = 256, SUNITS = 2;
+constexpr int SFTHR = 512, SUNITS = 1;
 
 template <typename T, int B>
 __global__ __launch_bounds__(SFTHR) void ilu0_small_lds_kernel(const int32_t* __restrict__ rows,
