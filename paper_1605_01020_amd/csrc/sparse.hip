@@ -408,6 +408,30 @@ __device__ __forceinline__ void strip_rmw(T* C, int b, int j0, const typename Mf
   }
 }
 
+// Value of lane h (uniform) of every quad, and the maximum over the wave of a
+// key that the lanes of a quad share: lane permutations (DPP) and reads, where
+// exchanges through LDS are five more round trips on the chain of a pivot
+// column (185 pivot blocks of 80 x 80, FP32: 63 us with those).
+template <int H>
+__device__ __forceinline__ int quad_i32(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, H * 0x55, 0xF, 0xF, true);
+}
+__device__ __forceinline__ int quad_value(int v, int h) {
+  const int a = h & 1 ? quad_i32<1>(v) : quad_i32<0>(v), b = h & 1 ? quad_i32<3>(v) : quad_i32<2>(v);
+  return h & 2 ? b : a;
+}
+__device__ __forceinline__ float quad_value(float v, int h) { return __int_as_float(quad_value(__float_as_int(v), h)); }
+__device__ __forceinline__ double quad_value(double v, int h) {
+  return __hiloint2double(quad_value(__double2hiint(v), h), quad_value(__double2loint(v), h));
+}
+__device__ __forceinline__ uint32_t quads_max(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, true));  // row_ror:4
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true));  // row_ror:8
+  const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16),
+                 c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+  return max(max(a, b), max(c, d));
+}
+
 template <typename T, int NB, bool VEC>
 __global__ __launch_bounds__(FTHR) void ilu0_row_kernel(int b, const int32_t* __restrict__ rows,
                                                         const int32_t* __restrict__ diag_slot,
@@ -492,12 +516,11 @@ __global__ __launch_bounds__(FTHR) void ilu0_row_kernel(int b, const int32_t* __
         const int par = k & 1;
         T v = T(0);
         if (active) {
-          v = __shfl(W[kk], (lane & ~3) | hk, kWave);  // entry (r, k)
+          v = quad_value(W[kk], hk);  // entry (r, k)
           float fm = fabsf((float)v);
           if (!(fm <= FLT_MAX)) fm = INFINITY;
           uint32_t key = (live && !pivoted) ? ((__float_as_uint(fm) & ~255u) | (uint32_t)(255 - r)) : 0u;
-#pragma unroll
-          for (int off = 4; off < 64; off <<= 1) key = max(key, (uint32_t)__shfl_xor((int)key, off, kWave));
+          key = quads_max(key);
           if (key != 0u && r == 255 - (int)(key & 255u)) {
             T* sl = slots + (par * 8 + wv) * SM::slot + h * CPT;
 #pragma unroll
