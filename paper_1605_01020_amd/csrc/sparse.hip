@@ -253,7 +253,7 @@ __global__ __launch_bounds__(THR) void sweep_kernel(int b, const int4* rows, con
 }
 
 // ---- BILU(0) factorisation ------------------------------------------------
-// One workgroup of FTHR threads per block row i of a level (section 2.2.2,
+// One workgroup of THR threads per block row i of a level (section 2.2.2,
 // BILU(0)).  For each lower slot (i, k) in elimination order:
 //   L_ik = A_ik U_kk^{-1}          (A_ik staged row-major in LDS, the product
 //                                   written to LDS and to M),
@@ -264,12 +264,17 @@ __global__ __launch_bounds__(THR) void sweep_kernel(int b, const int4* rows, con
 // consecutive k of one column of a column-major block) loaded from HBM as
 // vectors; the k index of the four MFMAs of a vector is permuted between
 // lanes, which reorders only the sum.  Strips of all updates of one slot are
-// dealt to the 8 waves.  The inversion is Gauss-Jordan with partial pivoting
+// dealt to the waves.  The inversion is Gauss-Jordan with partial pivoting
 // in exchange form, the block held in registers (4 threads per row, CPT
 // columns each) with one workgroup barrier per column: each wave posts its
 // best candidate row to LDS, so after the barrier every thread knows the
 // pivot row without a second exchange.
-constexpr int FTHR = 512;
+// THR: 512, or 1,024 for a level whose rows do not fill the CUs even once (a
+// row's strips then go to twice the waves), where the registers allow it: FP32,
+// b = 80, levels of 185 rows, whole factorisation 1.24 -> 1.12 ms.
+constexpr int FTHR = 512, FTHR_WIDE = 1024, kFewRows = 256;
+template <typename T, int NB, bool VEC>
+constexpr bool wide_rows() { return sizeof(T) == 4 || NB <= 4 || (NB == 5 && VEC); }
 
 template <typename T, int NB>
 struct FactorSmem {
@@ -294,20 +299,20 @@ __device__ __forceinline__ int frag_row(int li) {
 
 // Y[r * lda + c] = G[c * b + r] for r, c < b (a column-major block to
 // row-major LDS), 4 loads in flight per thread.
-template <typename T, int NB>
+template <typename T, int NB, int THR>
 __device__ __forceinline__ void stage_rowmajor(const T* __restrict__ G, T* Y, int b) {
   constexpr int lda = FactorSmem<T, NB>::lda;
   const int bb = b * b;
-  for (int q0 = threadIdx.x; q0 < bb; q0 += FTHR * 4) {
+  for (int q0 = threadIdx.x; q0 < bb; q0 += THR * 4) {
     T v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int q = q0 + FTHR * j;
+      const int q = q0 + THR * j;
       v[j] = q < bb ? G[q] : T(0);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int q = q0 + FTHR * j;
+      const int q = q0 + THR * j;
       if (q < bb) {
         const int c = q / b, r = q - c * b;
         Y[r * lda + c] = v[j];
@@ -432,8 +437,8 @@ __device__ __forceinline__ uint32_t quads_max(uint32_t v) {
   return max(max(a, b), max(c, d));
 }
 
-template <typename T, int NB, bool VEC>
-__global__ __launch_bounds__(FTHR) void ilu0_row_kernel(int b, const int32_t* __restrict__ rows,
+template <typename T, int NB, bool VEC, int THR>
+__global__ __launch_bounds__(THR) void ilu0_row_kernel(int b, const int32_t* __restrict__ rows,
                                                         const int32_t* __restrict__ diag_slot,
                                                         const int32_t* __restrict__ lptr,
                                                         const int32_t* __restrict__ lslot,
@@ -453,13 +458,13 @@ __global__ __launch_bounds__(FTHR) void ilu0_row_kernel(int b, const int32_t* __
   const int i = rows[blockIdx.x];
   const size_t bb = (size_t)b * b;
   // rows and columns of Y past b stay zero (finite operands where k >= b)
-  for (int q = tid; q < 16 * NB * lda; q += FTHR) Y[q] = T(0);
+  for (int q = tid; q < 16 * NB * lda; q += THR) Y[q] = T(0);
   __syncthreads();
   typename MF::acc_t acc[NB];
   for (int l = lptr[i]; l < lptr[i + 1]; ++l) {
     const int sik = lslot[2 * l], dk = lslot[2 * l + 1];
     T* Aik = M + (size_t)sik * bb;
-    stage_rowmajor<T, NB>(Aik, Y, b);
+    stage_rowmajor<T, NB, THR>(Aik, Y, b);
     __syncthreads();
     if (wv < NB) strip_mm<T, NB, VEC>(Y, M + (size_t)dk * bb, b, 16 * wv, acc);
     __syncthreads();  // every wave has read A_ik from Y
@@ -477,7 +482,7 @@ __global__ __launch_bounds__(FTHR) void ilu0_row_kernel(int b, const int32_t* __
     }
     __syncthreads();  // L_ik in Y
     const int u0 = uptr[l], nu = uptr[l + 1] - u0;
-    for (int w = wv; w < nu * NB; w += FTHR / 64) {
+    for (int w = wv; w < nu * NB; w += THR / 64) {
       const int u = u0 + w / NB, c = w - (w / NB) * NB;
       strip_mm<T, NB, VEC>(Y, M + (size_t)upd[2 * u] * bb, b, 16 * c, acc);
       strip_rmw<T, NB, VEC>(M + (size_t)upd[2 * u + 1] * bb, b, 16 * c, acc, true);
@@ -486,7 +491,7 @@ __global__ __launch_bounds__(FTHR) void ilu0_row_kernel(int b, const int32_t* __
   }
   // ---- pivot block: Gauss-Jordan inverse in exchange form ----
   T* Dg = M + (size_t)diag_slot[i] * bb;
-  stage_rowmajor<T, NB>(Dg, Y, b);
+  stage_rowmajor<T, NB, THR>(Dg, Y, b);
   __syncthreads();
   const int r = tid >> 2, h = tid & 3;  // row r, columns h CPT .. h CPT + CPT - 1
   const bool live = r < b;
@@ -572,7 +577,7 @@ __global__ __launch_bounds__(FTHR) void ilu0_row_kernel(int b, const int32_t* __
       if (c < b) Y[prow[c] * b + mystep] = W[j];
     }
   __syncthreads();
-  for (int q = tid; q < (int)bb; q += FTHR) Dg[q] = Y[q];
+  for (int q = tid; q < (int)bb; q += THR) Dg[q] = Y[q];
   if (!ok && tid == 0) latch_status(status, IEDG_ERR_SINGULAR, i);
 }
 
@@ -1025,14 +1030,21 @@ static iedg_status factor_levels_small(iedg_context ctx, iedg_mesh m, T* M, hipS
 template <typename T, int NB>
 static iedg_status factor_levels_nb(iedg_context ctx, iedg_mesh m, T* M, hipStream_t stream) {
   const size_t smem = FactorSmem<T, NB>::bytes;
-  auto kern = (m->b % 4 == 0) ? ilu0_row_kernel<T, NB, true> : ilu0_row_kernel<T, NB, false>;
-  IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)smem));
+  const bool vec = m->b % 4 == 0;
+  auto kern = vec ? ilu0_row_kernel<T, NB, true, FTHR> : ilu0_row_kernel<T, NB, false, FTHR>;
+  constexpr int WV = wide_rows<T, NB, true>() ? FTHR_WIDE : FTHR, WS = wide_rows<T, NB, false>() ? FTHR_WIDE : FTHR;
+  auto kern_wide = vec ? ilu0_row_kernel<T, NB, true, WV> : ilu0_row_kernel<T, NB, false, WS>;
+  const int wide_thr = vec ? WV : WS;
+  for (auto k : {kern, kern_wide})
+    IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)smem));
   for (int l = 0; l < m->n_levels; ++l) {
     const int r0 = m->level_ptr[l], cnt = m->level_ptr[l + 1] - r0;
     if (cnt == 0) continue;
-    hipLaunchKernelGGL(kern, dim3(cnt), dim3(FTHR), smem, stream, m->b, m->d_level_rows + r0, m->d_diag_slot,
-                       m->d_ilu_lptr, m->d_ilu_l, m->d_ilu_uptr, m->d_ilu_upd, M, ctx->d_status);
+    const bool wide = cnt <= kFewRows;
+    hipLaunchKernelGGL(wide ? kern_wide : kern, dim3(cnt), dim3(wide ? wide_thr : FTHR), smem, stream, m->b,
+                       m->d_level_rows + r0, m->d_diag_slot, m->d_ilu_lptr, m->d_ilu_l, m->d_ilu_uptr, m->d_ilu_upd, M,
+                       ctx->d_status);
     IEDG_LAUNCH_CHECK(ctx, "ilu0 level launch");
   }
   return IEDG_OK;
