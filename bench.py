@@ -16,7 +16,7 @@ K; mixed form: FP32 condensation / FP32 K and BILU(0), refined in FP64).
 Prints one JSON line.
 
 --workload batch: the 24-mesh uneven batch (mixed sizes and degrees), solved
-by the batched form (persistent condensation launches, HIP graph replay per
+by the batched form (one condensation launch sequence a size, HIP graph replay per
 memory group).  --workload serving: seeded Poisson requests against 64
 simulations under a 200 GB residency budget (continuous batching over HIP
 streams), reporting solves/s with p50/p99 latency.
@@ -36,10 +36,10 @@ FP32_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBS = 8000.0
 
 
-# the sources of the FP32 condensation kernel (HBM counters are reported only
+# the sources of the FP32 condensation kernels (HBM counters are reported only
 # while these are unchanged since the counters were taken)
-CONDENSE_SOURCES = ["paper_1605_01020_amd/csrc/condense_kernel.h", "paper_1605_01020_amd/csrc/condense.h",
-                    "paper_1605_01020_amd/csrc/condense_f32.hip", "paper_1605_01020_amd/csrc/condense_f32_single.hip",
+CONDENSE_SOURCES = ["paper_1605_01020_amd/csrc/condense_gemm.h", "paper_1605_01020_amd/csrc/condense.h",
+                    "paper_1605_01020_amd/csrc/condense_f32.hip", "paper_1605_01020_amd/csrc/condense_panel.hip",
                     "paper_1605_01020_amd/csrc/common.h",
                     "paper_1605_01020_amd/tuning.json"]
 
