@@ -43,7 +43,6 @@
 namespace iedg {
 
 constexpr int GT = 256;  // threads per workgroup of the tile kernels (4 waves)
-constexpr int KC = 32;   // k-slab depth
 
 // Round to nearest even FP32 -> BF16 (bit pattern); NaN stays NaN.
 __device__ __forceinline__ unsigned to_bf16(float f) {
@@ -64,10 +63,11 @@ typedef short bf16x4 __attribute__((ext_vector_type(4)));
 //
 // What bounds it: the matrix cores (FP32: 105 TFLOP/s of 155 where K is long,
 // 112 in the Schur block), and for short K the inputs, read in 1 KB pieces of
-// rows at 3 TB/s.  L is read a row at a time with rows far apart, so a slab is as deep as a cache line of
-// FP32 is long (16 deep, two slabs in LDS, left waves waiting 58% of the time
-// and the matrix cores busy 48%); one slab of that depth in LDS, and the next
-// in registers, keeps four FP32 workgroups a CU.
+// rows at 3 TB/s.  L is read a row at a time with rows far apart, so a slab is as deep as a
+// cache line is long, 32 in FP32 (16 deep, two slabs in LDS, left waves
+// waiting 58% of the time and the matrix cores busy 48%) and 16 in FP64 (32
+// deep costs a wave a SIMD: 512 elements of n = 1280 54.2 ms, 49.5 ms 16 deep).
+// One slab in LDS, and the next in registers.
 //
 // LDS, MM = 0: slabs k-major, A at As[k][row ^ swizzle(k)], B at
 // Bs[k][col ^ 16 (k & 3)]: the four k of a fragment read then lie in
@@ -76,6 +76,7 @@ typedef short bf16x4 __attribute__((ext_vector_type(4)));
 // a fragment is one 8-byte read.
 template <typename T, int MM, int TM, int TN, bool COLS>
 struct Tile {
+  static constexpr int KC = sizeof(T) == 8 ? 16 : 32;  // slab depth
   static constexpr int WR = COLS ? 1 : 2, WC = 4 / WR;
   static constexpr int WM = TM / WR, WN = TN / WC, RB = WM / 16, CB = WN / 16;
   static constexpr int V = 16 / sizeof(T);            // values per 16-byte vector
