@@ -16,7 +16,11 @@ constexpr int LWAVES = LTHR / 64;
 // keeps 16 loads in flight; 64-row diagonal blocks of U (fetched ahead of the
 // block's row sums by 1,024 threads) are staged in LDS in the storage precision and solved by
 // one wave.  A step of that solve is a lane read and four fused multiply-adds:
-// the quotient by the pivot is its reciprocal's product, corrected once.
+// the quotient by the pivot is its reciprocal's product, corrected once.  That
+// is a NaN where the reciprocal or the quotient is not finite (a zero, infinite
+// or subnormal pivot, an overflow): a block whose solution is not finite is
+// solved again with the quotients themselves, which keeps the test off the
+// chain of steps.
 template <typename T, int THR>
 __global__ __launch_bounds__(THR) void backsolve_kernel(int n, int t, int b, int S, const int32_t* elem_faces, const T* LU,
                                                         const int32_t* perm, const T* U12, const double* w,
@@ -91,8 +95,9 @@ __global__ __launch_bounds__(THR) void backsolve_kernel(int n, int t, int b, int
     }
     __syncthreads();
     if (wv == 0) {
-      double yl = lane < bw ? y[i0 + lane] : 0.0;
+      const double y0 = lane < bw ? y[i0 + lane] : 0.0;
       const double dg = lane < bw ? (double)blk[lane * 65 + lane] : 1.0, rd = 1.0 / dg;
+      double yl = y0;
 #pragma unroll 4
       for (int k = bw - 1; k >= 0; --k) {
         const double u = (double)blk[lane * 65 + k];
@@ -100,6 +105,14 @@ __global__ __launch_bounds__(THR) void backsolve_kernel(int n, int t, int b, int
         zl = fma(fma(-zl, dg, yl), rd, zl);
         const double zk = lane_value(zl, k);
         yl = lane == k ? zk : lane < k ? fma(-u, zk, yl) : yl;
+      }
+      if (__ballot(lane < bw && !isfinite(yl))) {
+        yl = y0;
+        for (int k = bw - 1; k >= 0; --k) {
+          const double u = (double)blk[lane * 65 + k];
+          const double zk = lane_value(yl, k) / lane_value(dg, k);
+          yl = lane == k ? zk : lane < k ? fma(-u, zk, yl) : yl;
+        }
       }
       if (lane < bw) y[i0 + lane] = yl;
     }
