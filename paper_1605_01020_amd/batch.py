@@ -322,15 +322,21 @@ class BatchGroup:
         for pl in self.plans:
             pl.run()
         here = torch.cuda.current_stream()
-        for st, sims in zip(self.streams, self.branches[1:]):
-            st.wait_stream(here)
-            with torch.cuda.stream(st):
-                for s in sims:
-                    s.enqueue_after_condense()
-        for s in self.branches[0] if self.branches else []:
-            s.enqueue_after_condense()
-        for st in self.streams:
-            here.wait_stream(st)
+        forked = []
+        try:
+            for st, sims in zip(self.streams, self.branches[1:]):
+                forked.append(st)
+                st.wait_stream(here)
+                with torch.cuda.stream(st):
+                    for s in sims:
+                        s.enqueue_after_condense()
+            for s in self.branches[0] if self.branches else []:
+                s.enqueue_after_condense()
+        finally:
+            # also when a launch is refused: what the branches have queued
+            # still writes arrays the caller may free or reuse
+            for st in forked:
+                here.wait_stream(st)
 
     def capture(self):
         """Capture enqueue() in a graph (after an eager run has set up every

@@ -42,3 +42,102 @@ def test_poisson_requests_are_seeded_and_poisson():
     for r in a:
         seen[r.sim] = seen.get(r.sim, 0) + 1
         assert r.rhs == seen[r.sim]
+
+
+class _Stream:
+    """Stands in for a stream: notes what is queued and whom it waits for."""
+
+    def __init__(self, log):
+        self.log = log
+
+    def wait_stream(self, other):
+        self.log.append(("wait", self, other))
+
+
+class _Sim:
+    def __init__(self, log, streams, n_trace, gm=None, mesh=None, fails=False):
+        self.log, self.streams, self.fails = log, streams, fails
+        self.gm = [object()] if gm is None else gm
+        self.mesh = type("M", (), {"n_trace": n_trace})() if mesh is None else mesh
+
+    def enqueue_after_condense(self):
+        if self.fails:
+            raise RuntimeError("refused")
+        self.log.append(("solve", self, self.streams[-1]))
+
+
+def _group(monkeypatch, sims, log, streams):
+    """A BatchGroup over stand-ins: no library, no GPU."""
+    import contextlib
+    from paper_1605_01020_amd import batch
+
+    @contextlib.contextmanager
+    def on(st):
+        streams.append(st)
+        try:
+            yield
+        finally:
+            streams.pop()
+
+    monkeypatch.setattr(batch.torch.cuda, "current_stream", lambda: streams[-1])
+    monkeypatch.setattr(batch.torch.cuda, "stream", on)
+    g = batch.BatchGroup.__new__(batch.BatchGroup)
+    g.sims, g.plans = sims, []
+    g.branches = g._branches()
+    g.streams = [_Stream(log) for _ in g.branches[1:]]
+    return g
+
+
+@pytest.mark.parametrize("failing", [None, 0, 1, 2, 4])
+def test_batch_group_joins_every_branch(monkeypatch, failing):
+    """Every stream that was forked from the caller's is joined to it at the
+    end, also when a mesh's solve is refused on any branch."""
+    log = []
+    here = _Stream(log)
+    streams = [here]
+    sims = [_Sim(log, streams, 100 - i, fails=i == failing) for i in range(5)]
+    g = _group(monkeypatch, sims, log, streams)
+    if failing is None:
+        g.enqueue()
+    else:
+        with pytest.raises(RuntimeError, match="refused"):
+            g.enqueue()
+    assert streams == [here]
+    used = {e[2] for e in log if e[0] == "solve"} - {here}
+    for st in used | {s for s in g.streams if ("wait", s, here) in log}:
+        last = max((i for i, e in enumerate(log) if e[0] == "solve" and e[2] is st), default=-1)
+        assert ("wait", here, st) in log[last + 1:], "a branch is left unjoined"
+    if failing is None:
+        assert len([e for e in log if e[0] == "solve"]) == 5 and len(g.streams) == 3
+
+
+def test_batch_group_branches(monkeypatch):
+    """Meshes that share a workspace stay on one branch, in their order: a
+    shared mesh, a shared GMRES state, and chains of both."""
+    log, streams = [], [None]
+
+    def sim(n, **k):
+        return _Sim(log, streams, n, **k)
+
+    def deal(sims):
+        g = _group(monkeypatch, sims, log, streams)
+        assert sorted(map(id, sims)) == sorted(id(s) for b in g.branches for s in b)
+        assert all(g.branches) and len(g.branches) <= g.BRANCHES
+        return {id(s): k for k, b in enumerate(g.branches) for s in b}, g.branches
+
+    assert deal([])[1] == []
+    assert len(deal([sim(5)])[1]) == 1
+    assert len(deal([sim(5), sim(4), sim(3)])[1]) == 3
+    assert len(deal([sim(n) for n in range(9, 0, -1)])[1]) == 4
+    a, b = sim(7), sim(6)
+    c = sim(5, mesh=a.mesh)                    # a's mesh
+    d = sim(4, gm=[b.gm[0], object()])         # b's GMRES state
+    where, br = deal([a, b, c, d])
+    assert where[id(a)] == where[id(c)] != where[id(b)] == where[id(d)]
+    assert all(x.index(p) < x.index(q) for x in br for p, q in ((a, c), (b, d)) if p in x)
+    e = sim(3, gm=[a.gm[0], d.gm[1]])          # joins both chains
+    where, br = deal([a, b, c, d, e, sim(2)])
+    assert len({where[id(s)] for s in (a, b, c, d, e)}) == 1 and len(br) == 2
+    one = next(x for x in br if a in x)
+    for p, q in ((a, c), (b, d), (a, e), (d, e)):
+        assert one.index(p) < one.index(q)
