@@ -141,7 +141,9 @@ iedg_status iedg_mesh_query(iedg_mesh mesh, iedg_mesh_info* info, int32_t* order
  *   L21, Ke and r are indexed by the rows of C.
  * Outputs must not overlap inputs or each other (Ke holds intermediate values
  * until the Schur complement is written).  A zero or non-finite pivot latches
- * IEDG_ERR_SINGULAR with the element index.
+ * IEDG_ERR_SINGULAR with the element index; the rows of U, U12 and w before
+ * that pivot are those of the factorisation, the rest of that element is
+ * undefined.
  * Limits: n a multiple of 4 and at most 2560, t even and at most 1024
  * (IEDG_ERR_UNSUPPORTED otherwise); every array 16-byte aligned, as device
  * allocators return it (IEDG_ERR_INVALID_ARG otherwise). */

@@ -144,6 +144,42 @@ inline dim3 condense_grid(const CondenseWork<T>& wk, int tiles) {
   return dim3((unsigned)((wk.spread ? wk.count : (wk.count + 7) / 8 * 8) * tiles));
 }
 
+// ---- growing L_pp^{-1} where L may hold infinities or NaN -----------------------
+// As grow_inverse, for an element without a pivot: the zeros of whole blocks
+// would spread them to rows that do not depend on them, so every entry takes
+// the products of the triangles alone, in the same order.
+template <typename T>
+__device__ __forceinline__ void grow_inverse_entries(T* Li, int LS, const T* Lb, T* Y, int kp, int sw) {
+  int tid = threadIdx.x, nt = blockDim.x;
+  asm volatile("" : "+v"(tid));  // (cold: nothing of it is computed ahead and kept)
+#pragma unroll 1
+  for (int o = tid; o < sw * kp; o += nt) {
+    const int i = o / kp, k = o % kp;
+    T acc = T(0);
+#pragma unroll 1
+    for (int m = k; m < kp; ++m) acc = fma(Lb[i * 64 + m], Li[m * LS + k], acc);
+    Y[i * 64 + k] = acc;
+  }
+  if (tid < sw)
+#pragma unroll 1
+    for (int i = tid; i < sw; ++i) {
+      T acc = i == tid ? T(1) : T(0);
+#pragma unroll 1
+      for (int m = tid; m < i; ++m) acc = fma(-Lb[i * 64 + kp + m], Li[(kp + m) * LS + kp + tid], acc);
+      Li[(kp + i) * LS + kp + tid] = acc;
+    }
+  __syncthreads();
+#pragma unroll 1
+  for (int o = tid; o < sw * kp; o += nt) {
+    const int i = o / kp, k = o % kp;
+    T acc = T(0);
+#pragma unroll 1
+    for (int m = 0; m <= i; ++m) acc = fma(Li[(kp + i) * LS + kp + m], Y[m * 64 + k], acc);
+    Li[(kp + i) * LS + k] = -acc;
+  }
+  __syncthreads();
+}
+
 // ---- growing L_pp^{-1} ---------------------------------------------------
 // Rows kp .. kp+sw of the inverse of a unit lower triangle from rows 0 .. kp
 // of it (Li, stride LS, zero above the diagonal and in rows >= kp) and the
@@ -155,9 +191,14 @@ inline dim3 condense_grid(const CondenseWork<T>& wk, int tiles) {
 // one nonzero k, while others form L21 L11^{-1}: in vector registers its rows
 // would cost more than the rest of the growth.  Y: LW x 64 of LDS.  Called by
 // every thread; ends with a barrier.
+// odd (uniform): L may hold infinities or NaN; grow_inverse_entries then.
 template <typename T, int LW>
-__device__ __forceinline__ void grow_inverse(T* Li, int LS, const T* Lb, T* Y, int kp, int sw) {
+__device__ __forceinline__ void grow_inverse(T* Li, int LS, const T* Lb, T* Y, int kp, int sw, bool odd) {
   typedef Mfma<T> MF;
+  if (__builtin_expect(odd, 0)) {
+    grow_inverse_entries<T>(Li, LS, Lb, Y, kp, sw);
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
   const int kb = (kp + 15) / 16;  // column blocks of the finished part (at most 3)
@@ -217,11 +258,33 @@ __device__ __forceinline__ void grow_inverse(T* Li, int LS, const T* Lb, T* Y, i
 // The bottom-left block of a 128-wide panel's inverse, -L22^{-1} (L21 L11^{-1}):
 // inv11 (64 x 64, stride s1) and inv22 (wr x wr in a 64 x 64 block, stride s2)
 // are the halves' inverses, l21(i, k) reads L21.  Y: 64 x 65 of LDS; out:
-// 64 x 64, rows >= wr zero.  Called by every thread; ends with a barrier.
+// 64 x 64, rows >= wr zero.  odd: as for grow_inverse, entry by entry.  Called by
+// every thread; ends with a barrier.
 template <typename T, typename F>
 __device__ __forceinline__ void inverse_offdiag(const T* inv11, int s1, const T* inv22, int s2, int wr, F l21, T* Y,
-                                                T* out) {
+                                                T* out, bool odd) {
   typedef Mfma<T> MF;
+  if (__builtin_expect(odd, 0)) {
+#pragma unroll 1
+    for (int o = threadIdx.x; o < 64 * wr; o += blockDim.x) {
+      const int i = o >> 6, k = o & 63;
+      T acc = T(0);
+#pragma unroll 1
+      for (int m = k; m < 64; ++m) acc = fma(l21(i, m), inv11[m * s1 + k], acc);
+      Y[i * 65 + k] = acc;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int o = threadIdx.x; o < 64 * 64; o += blockDim.x) {
+      const int i = o >> 6, k = o & 63;
+      T acc = T(0);
+#pragma unroll 1
+      for (int m = 0; m <= i && i < wr; ++m) acc = fma(inv22[i * s2 + m], Y[m * 65 + k], acc);
+      out[o] = -acc;
+    }
+    __syncthreads();
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
   for (int b = wv; b < 16; b += nw) {

@@ -425,22 +425,25 @@ __global__ __launch_bounds__(GT, sizeof(T) == 8 ? 2 : 3) void condense_row_kerne
     T* Y = Lb + LW * 64;
     for (int i = tid; i < (CT == 128 ? 3 : 1) * kInvBlock; i += GT) Li[i] = T(0);
     __syncthreads();
+    bool odd = false;  // an infinity or NaN in L (of an element without a pivot)
     for (int h = 0; h < wp; h += 64)
       for (int kp = 0; kp < min(64, wp - h); kp += LW) {
         const int sw = min(LW, min(64, wp - h) - kp);
         for (int o = tid; o < sw * (kp + sw); o += GT) {
           const int i = o / (kp + sw), k = o % (kp + sw);
-          Lb[i * 64 + k] = k < kp + i ? el.LU[(size_t)rp[h + kp + i] * n + c0 + h + k] : T(0);
+          const T l = k < kp + i ? el.LU[(size_t)rp[h + kp + i] * n + c0 + h + k] : T(0);
+          odd |= !isfinite(l);
+          Lb[i * 64 + k] = l;
         }
-        __syncthreads();
-        grow_inverse<T, LW>(h ? Li + 2 * kInvBlock : Li, 64, Lb, Y, kp, sw);
+        odd = __syncthreads_or(odd);
+        grow_inverse<T, LW>(h ? Li + 2 * kInvBlock : Li, 64, Lb, Y, kp, sw, odd);
       }
     if (CT == 128 && wp > 64)
       inverse_offdiag<T>(Li, 64, Li + 2 * kInvBlock, 64, wp - 64,
                          [&](int i, int k) __attribute__((always_inline)) {
                            return el.LU[(size_t)rp[64 + i] * n + c0 + k];
                          },
-                         Y, Li + kInvBlock);
+                         Y, Li + kInvBlock, odd);
     inv = Li;
   }
 

@@ -24,6 +24,15 @@
 // vector FMAs with the same bits, and the pivot row is read as one vector per
 // lane in place of LW broadcasts.  (v_mfma_f64_4x4x4 has no such form: FP64
 // rows take vector FMAs.)
+//
+// Infinities and NaN (of an element without a pivot) stay where elimination
+// entry by entry has them: rows before them keep their values.  Zeros of whole
+// blocks would spread them, so products that come out not finite are formed
+// again without those zeros, U rows that met an infinity in a rank-one update
+// are put back, and the inverse grows entry by entry from the first missing
+// pivot on.  None of it is on the chain of pivot columns (8 elements of
+// n = 160, FP32 256 -> 261 us, FP64 335 -> 337 us; 256 of n = 1280, FP32 the
+// same, FP64 25.4 -> 25.6 ms).
 #include <climits>
 
 #include "condense.h"
@@ -115,13 +124,17 @@ struct PanelSmem {
   T Xu[64 * LW];         // rows above the sub-panel (input), then LW x 64 of scratch
   T Ut[64 * LW];         // U rows above the sub-panel, each in row_slot order
   T Lb[LW * 64];         // L rows of the sub-panel
-  T cand[2][NW][LW];     // each wave's best candidate row, by column parity
-  T krow[2][LW];         // row at the pivot position where no pivot was found, its entry
+  // each wave's best candidate row, by column (FP32) or its parity
+  static constexpr int COLS = sizeof(T) == 4 ? LW : 2;
+  T cand[COLS][NW][LW];
+  T krow[LW];            // row at the pivot position where no pivot was found (FP64)
+  T kval;                // and its entry
   T cval[2][NW];         // the candidates' pivot entries
   int cidx[2][NW];       // and positions
   int prow[64];          // physical rows of the panel's pivots
   T* rowp[NT * R];       // every row slot's row in LU or L21 (LU past the last)
   int phys[NT * R];      // and its physical row (rows of A)
+  int odd;               // a pivot row was not finite (FP32)
 };
 
 // A row's columns in registers, in quads (the FP32 rank-one update's
@@ -134,6 +147,20 @@ struct DoubleQuad {
 template <typename T> struct Quad;
 template <> struct Quad<float> { typedef f4 v; };
 template <> struct Quad<double> { typedef DoubleQuad v; };
+
+// Whether any entry of the wave's accumulator is not finite.
+template <typename V>
+__device__ __forceinline__ bool any_nonfinite(const V& a) {
+  return __ballot(!(isfinite(a[0]) && isfinite(a[1]) && isfinite(a[2]) && isfinite(a[3]))) != 0;
+}
+
+// What the pivot columns of a sub-panel leave (uniform): none: a column had no
+// pivot, so L may hold infinities or NaN; win: which wave's post is the pivot
+// row, four bits a column.
+struct Trail {
+  bool none;
+  unsigned long long win;
+};
 
 // x -= l u over a row's columns past KK (KK < 0: all), u in the lane's share
 // layout with the columns up to KK zero.
@@ -165,8 +192,8 @@ __device__ __forceinline__ void put_row(const Q4 (&x)[R][LW / 4], int q, int kk,
 // pos[q] the position of slot q's row.
 template <typename T, int LW, int R, int NT, int KK>
 __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, R, NT>& sm, typename Quad<T>::v (&x)[R][LW / 4], int (&pos)[R],
-                                             int k, int n, DeviceStatus* status, int elem) {
-  constexpr int NW = NT / 64, par = KK & 1;
+                                             int k, int n, DeviceStatus* status, int elem, Trail& tr) {
+  constexpr int NW = NT / 64, par = KK & 1, col = KK % PanelSmem<T, LW, R, NT>::COLS;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the thread's candidate among the rows of A at positions >= k: largest
@@ -189,7 +216,7 @@ __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, R, NT>& sm, typena
     const int win = best_lane(__ballot(key == kmax), best, bpos);
     const int sq = read_lane(bq, win);
     if (lane == win) {
-      put_row<LW, 0>(x, sq, KK, sm.cand[par][wv], &sm.cval[par][wv]);
+      put_row<LW, 0>(x, sq, KK, sm.cand[col][wv], &sm.cval[par][wv]);
       sm.cidx[par][wv] = bpos;
     }
   }
@@ -204,21 +231,30 @@ __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, R, NT>& sm, typena
   const T ca = ci == INT_MAX ? T(-1) : fabs(cv);
   const unsigned ckey = mag_key(ca), gkey = read_lane(row_max(ckey), 0);
   const int bw = best_lane(__ballot(ckey == gkey) & ((1ull << NW) - 1), ca, ci);
-  int piv = read_lane(ci, bw);
+  int piv = read_lane(ci, bw), from = bw;
   T rinv = read_lane(cinv, bw);
   const T gbest = read_lane(ca, bw);
-  const T* urow = sm.cand[par][bw];
+  const T* urow = sm.cand[col][bw];
   if (!(gbest > T(0)) || !isfinite(gbest)) {
     // no pivot: row k stays (the branch is uniform over the workgroup)
     if (tid == 0) latch_status(status, IEDG_ERR_SINGULAR, elem);
+    tr.none = true;
+    from = 0;  // (FP32: posted in place of a candidate, as its pivot row)
+    T* row;
+    if constexpr (sizeof(T) == 4) row = sm.cand[col][0];
+    else row = sm.krow;
 #pragma unroll
     for (int q = 0; q < R; ++q)
-      if (pos[q] == k) put_row<LW, 0>(x, q, KK, sm.krow[0], &sm.krow[1][0]);
+      if (pos[q] == k) put_row<LW, 0>(x, q, KK, row, &sm.kval);
     __syncthreads();
     piv = k;
-    urow = sm.krow[0];
-    rinv = T(1) / sm.krow[1][0];
+    urow = row;
+    rinv = T(1) / sm.kval;
     __syncthreads();  // read before another column posts its row k
+  }
+  if constexpr (sizeof(T) == 4) {
+    urow = sm.cand[col][from];
+    tr.win |= (unsigned long long)from << (4 * KK);
   }
 #pragma unroll
   for (int q = 0; q < R; ++q) pos[q] = pos[q] == piv ? k : pos[q] == k ? piv : pos[q];
@@ -230,8 +266,8 @@ __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, R, NT>& sm, typena
       u[c] = urow[(lane & 3) * (LW / 4) + c];
       if (c == KK / 4) u[c] = 4 * c + (lane & 3) > KK ? u[c] : T(0);
     }
-    // (rows that stay take 0 times u: where u is not finite, which leaves the
-    // element without a usable U in any case, their later entries turn NaN)
+    // (rows that stay take 0 times u: where u is not finite they are put back
+    // after the sub-panel)
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       const bool live = pos[q] > k;
@@ -257,12 +293,12 @@ __device__ __forceinline__ void pivot_column(PanelSmem<T, LW, R, NT>& sm, typena
 
 template <typename T, int LW, int R, int NT, int KK>
 __device__ __forceinline__ void pivot_columns(PanelSmem<T, LW, R, NT>& sm, typename Quad<T>::v (&x)[R][LW / 4], int (&pos)[R],
-                                              int cs, int sw, int n, DeviceStatus* status, int elem) {
+                                              int cs, int sw, int n, DeviceStatus* status, int elem, Trail& tr) {
   if constexpr (KK < LW) {
     if constexpr (KK % 4 == 0)  // sw is a multiple of 4, as n is
       if (KK >= sw) return;
-    pivot_column<T, LW, R, NT, KK>(sm, x, pos, cs + KK, n, status, elem);
-    pivot_columns<T, LW, R, NT, KK + 1>(sm, x, pos, cs, sw, n, status, elem);
+    pivot_column<T, LW, R, NT, KK>(sm, x, pos, cs + KK, n, status, elem, tr);
+    pivot_columns<T, LW, R, NT, KK + 1>(sm, x, pos, cs, sw, n, status, elem, tr);
   }
 }
 
@@ -291,6 +327,7 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
     sm.rowp[tid + NT * q] = p < N ? el.lrow(p, phys) : el.LU;
   }
   for (int i = tid; i < 64 * LIS; i += NT) sm.Li[i] = T(0);
+  if (tid == 0) sm.odd = 0;
   __syncthreads();
 
   // Rows move between memory and lanes in 16-row groups: four lanes (one of
@@ -336,6 +373,7 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
   unsigned raw[R][4][CD];
 #pragma unroll
   for (int q = 0; q < R; ++q) fetch(q, cb, min(LW, wp), raw[q]);
+  bool odd = false;  // a column so far had no pivot
   for (int cs = cb; cs < ce; cs += LW) {
     const int sw = min(LW, ce - cs), kp = cs - cb;
     Q4 x[R][LW / 4];
@@ -355,6 +393,19 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
         for (int m = 0; m < 16 * (ib + 1); m += 4) {
           const T bv = li < LW && m + lg < kp ? sm.Xu[(m + lg) * LW + (li & (LW - 1))] : T(0);
           acc = MF::mac(sm.Li[(16 * ib + li) * LIS + m + lg], bv, acc);
+        }
+        if (__builtin_expect(any_nonfinite(acc), 0)) {  // (the zeros above the diagonal met an infinity)
+          int ln = lane;
+          asm volatile("" : "+v"(ln));  // (cold: nothing of it is computed ahead and kept)
+#pragma unroll 1
+          for (int v = 0; v < 4; ++v) {
+            const int i = 16 * ib + MF::row(ln, v);
+            T s = T(0);
+#pragma unroll 1
+            for (int m = 0; m <= min(i, kp - 1); ++m) s = fma(sm.Li[i * LIS + m], sm.Xu[m * LW + (ln & (LW - 1))], s);
+            acc[0] = v == 0 ? s : acc[0]; acc[1] = v == 1 ? s : acc[1];
+            acc[2] = v == 2 ? s : acc[2]; acc[3] = v == 3 ? s : acc[3];
+          }
         }
         if (li < LW) {
 #pragma unroll
@@ -395,7 +446,9 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
           for (int j = 0; j < LW; ++j) x[q][j / 4][j % 4] = sm.Ut[(pos[q] - cb) * LW + row_slot<LW>(j)];
         }
     }
-    pivot_columns<T, LW, R, NT, 0>(sm, x, pos, cs, sw, n, el.status, el.id);
+    Trail tr = {false, 0};
+    pivot_columns<T, LW, R, NT, 0>(sm, x, pos, cs, sw, n, el.status, el.id, tr);
+    odd |= tr.none;
     const bool inverse = !wk.self || cs + LW < ce || right > 0;  // needed further
     // where the pivot rows are, and their own columns of L
 #pragma unroll
@@ -403,14 +456,33 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
       const int i = pos[q] - cs;
       if (i >= 0 && i < sw) {
         sm.prow[kp + i] = sm.phys[tid + NT * q];
+        T sum = T(0);
 #pragma unroll
-        for (int j = 0; j < LW; ++j)
+        for (int j = 0; j < LW; ++j) {
+          if constexpr (sizeof(T) == 4) sum += fabs(x[q][j / 4][j % 4]);
           if (j < sw) sm.Lb[i * 64 + kp + j] = j < i ? x[q][j / 4][j % 4] : T(0);
+        }
+        if constexpr (sizeof(T) == 4)
+          if (!isfinite(sum)) sm.odd = 1;
       }
     }
     // (nothing but earlier sub-panels' stores is in flight: the wait is short,
     // and the rows below are read by other waves than stored them)
     sync_global();
+    if constexpr (sizeof(T) == 4) {
+      if (__builtin_expect(__builtin_amdgcn_readfirstlane(sm.odd), 0)) {
+        // a pivot row is not finite, and rows of U took 0 times its entries:
+        // back as they were posted, or as they came
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          const int i = pos[q] - cs;
+          if (i >= sw) continue;
+          const T* row = i < 0 ? sm.Ut + (kp + i) * LW : sm.cand[i][(tr.win >> (4 * i)) & 15];
+#pragma unroll
+          for (int j = 0; j < LW; ++j) x[q][j / 4][j % 4] = row[row_slot<LW>(j)];
+        }
+      }
+    }
     constexpr int LBV = (LW * 64 + NT - 1) / NT;
     T lb[LBV];
     if (inverse) {  // the panel's earlier columns of the pivot rows
@@ -462,7 +534,7 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
         if (i < sw && k < kp) sm.Lb[i * 64 + k] = lb[v];
       }
       __syncthreads();
-      grow_inverse<T, LW>(sm.Li, LIS, sm.Lb, sm.Xu, kp, sw);
+      grow_inverse<T, LW>(sm.Li, LIS, sm.Lb, sm.Xu, kp, sw, odd);
     }
   }
 #pragma unroll
@@ -481,11 +553,22 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
 #pragma unroll
         for (int q = 0; q < 16; ++q) xb[q] = ok ? el.LU[(size_t)prow[4 * q + lg] * n + col] : T(0);
 #pragma unroll
-        for (int ib = 0; ib < 4; ++ib) {
+        for (int ib = 3; ib >= 0; --ib) {  // (from the last: X is overwritten, and read again below)
           typename MF::acc_t acc = MF::zero();
 #pragma unroll
           for (int q = 0; q < 4 * (ib + 1); ++q)
             acc = MF::mac(sm.Li[(16 * ib + li) * LIS + 4 * q + lg], xb[q], acc);
+          if (__builtin_expect(any_nonfinite(acc), 0)) {
+#pragma unroll 1
+            for (int v = 0; v < 4; ++v) {
+              const int i = 16 * ib + MF::row(lane, v);
+              T s = T(0);
+#pragma unroll 1
+              for (int m = 0; m <= i; ++m) s = fma(sm.Li[i * LIS + m], ok ? el.LU[(size_t)prow[m] * n + col] : T(0), s);
+              acc[0] = v == 0 ? s : acc[0]; acc[1] = v == 1 ? s : acc[1];
+              acc[2] = v == 2 ? s : acc[2]; acc[3] = v == 3 ? s : acc[3];
+            }
+          }
           if (ok) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) el.LU[(size_t)prow[16 * ib + MF::row(lane, v)] * n + col] = acc[v];
@@ -505,7 +588,7 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
       T* Y = reinterpret_cast<T*>(smem_raw + ((sizeof(SM) + 15) & ~size_t(15)));
       inverse_offdiag<T>(el.Ke, 64, sm.Li, LIS, wp,
                          [&](int i, int k) __attribute__((always_inline)) { return lu[(size_t)sp[i] * n + c0 + k]; }, Y,
-                         el.Ke + kInvBlock);
+                         el.Ke + kInvBlock, odd);
     }
   }
 }
