@@ -143,6 +143,10 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 constexpr int kElementWide = 1024, kElementNarrow = 256;
 inline bool element_wide(int n_elem) { return n_elem <= 512; }
 
+// Workgroups of `threads` threads one launch can have: its threads are counted
+// in 32 bits, and a larger grid is cut short without an error.
+constexpr int64_t launch_groups(int threads) { return (int64_t)UINT32_MAX / threads; }
+
 // Device status word: the smallest failing index (element or block row)
 // and its code in one 64-bit word, (index << 8) | -code, all ones when
 // clear, so that one atomicMin keeps an index with its own code whatever

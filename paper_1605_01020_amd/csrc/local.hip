@@ -277,17 +277,23 @@ static iedg_status residual_launch(iedg_context ctx, iedg_mesh mesh, int n, cons
   double* pg = prg + NF;
   const size_t smem = sizeof(double) * (t + n + LWAVES);
   // rF written over F or z: the whole element in one workgroup, which reads
-  // both before it writes
+  // both before it writes (and where the split would be too many workgroups)
   const double* last = rF + (size_t)E * n;
   const bool over = (F < last && rF < F + (size_t)E * n) || (z < last && rF < z + (size_t)E * n);
-  const int rows = over ? n + t : RROWS, chunks = (n + t + rows - 1) / rows;
-  if ((int64_t)E * chunks > INT32_MAX) return set_error(ctx, IEDG_ERR_UNSUPPORTED, "residual: %d elements of n=%d", E, n);
+  const int split = (n + t + RROWS - 1) / RROWS;
+  const bool whole = over || (int64_t)E * split > launch_groups(LTHR);
+  const int rows = whole ? n + t : RROWS, chunks = whole ? 1 : split;
   IEDG_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(residual_elem_kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
   hipLaunchKernelGGL(residual_elem_kernel, dim3(E * chunks), dim3(LTHR), smem, stream, n, t, b, mesh->slots, rows, chunks,
                      mesh->d_elem_faces, A, B, C, D, F, z, uhat, rF, q, pf);
-  hipLaunchKernelGGL(residual_face_kernel, dim3(NF + E), dim3(128), 0, stream, NF, n, b, t, mesh->slots, mesh->d_src_ptr,
-                     mesh->d_src_list, q, G, rF, rG, prg, pg, prf);
+  // units and elements in one launch, or one launch each
+  const bool one = (int64_t)NF + E <= launch_groups(128);
+  hipLaunchKernelGGL(residual_face_kernel, dim3(one ? NF + E : NF), dim3(128), 0, stream, NF, n, b, t, mesh->slots,
+                     mesh->d_src_ptr, mesh->d_src_list, q, G, rF, rG, prg, pg, prf);
+  if (!one)
+    hipLaunchKernelGGL(residual_face_kernel, dim3(E), dim3(128), 0, stream, 0, n, b, t, mesh->slots, mesh->d_src_ptr,
+                       mesh->d_src_list, q, G, rF, rG, prg, pg, prf);
   hipLaunchKernelGGL(sum4_kernel, dim3(4), dim3(64), 0, stream, prf, (int64_t)E, prg, (int64_t)NF, pf, (int64_t)E, pg,
                      (int64_t)NF, sums);
   IEDG_LAUNCH_CHECK(ctx, "residual launch");

@@ -596,8 +596,10 @@ template <typename T>
 static void spmv_run(iedg_mesh m, const void* K, const double* x, const double* rhs, double* y, int mode,
                      hipStream_t stream, const int* skip) {
 #define IEDG_SPMV(CS, THR)                                                                                       \
-  hipLaunchKernelGGL((spmv_kernel<T, CS, THR>), dim3(m->n_face), dim3(THR), 0, stream, m->b, m->d_row_face,      \
-                     m->d_row_ptr, m->d_col_face, (const T*)K, x, rhs, y, mode, skip)
+  for (int64_t r0 = 0; r0 < m->n_face; r0 += launch_groups(THR))                                                 \
+  hipLaunchKernelGGL((spmv_kernel<T, CS, THR>), dim3(std::min<int64_t>(m->n_face - r0, launch_groups(THR))),     \
+                     dim3(THR), 0, stream, m->b, m->d_row_face + r0, m->d_row_ptr + r0, m->d_col_face,           \
+                     (const T*)K, x, rhs, y, mode, skip)
   // (blocks up to 8 wide are one unit each in any case)
   if (m->b <= 8) IEDG_SPMV(8, PTHR);
   else if (m->n_face < kManyRows) IEDG_SPMV(16, PTHR);
@@ -1014,9 +1016,10 @@ static iedg_status factor_levels_small(iedg_context ctx, iedg_mesh m, T* M, hipS
     }
     const size_t lds = blk * (size_t)len + sizeof(int) * (3 * (size_t)len + 1);
     if (lds <= kSmallRowLds) {
-      hipLaunchKernelGGL(kern_lds, dim3(cnt), dim3(SFTHR), lds, stream, m->d_level_rows + r0, m->d_row_ptr,
-                         m->d_diag_slot, m->d_ilu_lptr, m->d_ilu_l, m->d_ilu_uptr,
-                         reinterpret_cast<const int2*>(m->d_ilu_upd), M, ctx->d_status);
+      for (int64_t k0 = 0; k0 < cnt; k0 += launch_groups(SFTHR))
+        hipLaunchKernelGGL(kern_lds, dim3(std::min<int64_t>(cnt - k0, launch_groups(SFTHR))), dim3(SFTHR), lds, stream,
+                           m->d_level_rows + r0 + k0, m->d_row_ptr, m->d_diag_slot, m->d_ilu_lptr, m->d_ilu_l,
+                           m->d_ilu_uptr, reinterpret_cast<const int2*>(m->d_ilu_upd), M, ctx->d_status);
     } else {
       hipLaunchKernelGGL(kern, dim3((cnt + 3) / 4), dim3(256), 0, stream, cnt,
                          m->d_level_rows + r0, m->d_diag_slot, m->d_ilu_lptr, m->d_ilu_l, m->d_ilu_uptr,
