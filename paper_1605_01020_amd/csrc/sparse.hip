@@ -835,6 +835,10 @@ __global__ __launch_bounds__(256) void ilu0_small_kernel(int nrows, const int32_
 // a lane, 72 us with 256 threads of two units, 48 us with 512 of one.
 // Dynamic LDS: the longest row of the level, in blocks, and its slot lists.
 constexpr int SFTHR = 512, SUNITS = 1;
+// First value of a slot in its row's LDS copy: the slot counts the whole
+// matrix (up to 2^31 - 1), so it is made the row's own before it is multiplied.
+__host__ __device__ constexpr int row_value(int slot, int first, int bb) { return (slot - first) * bb; }
+static_assert(row_value(90000005, 90000000, 25) == 125, "slots past 2^31 / B^2");
 
 template <typename T, int B>
 __global__ __launch_bounds__(SFTHR) void ilu0_small_lds_kernel(const int32_t* __restrict__ rows,
@@ -904,7 +908,7 @@ __global__ __launch_bounds__(SFTHR) void ilu0_small_lds_kernel(const int32_t* __
 #pragma unroll
     for (int r = 0; r < SUNITS; ++r) id[r] = idn[r];
     fetch_ids(l + 2, idn);
-    T* Lk = R + sl[2 * l] * BB - s0 * BB;
+    T* Lk = R + row_value(sl[2 * l], s0, BB);
     if (lane < BB) {  // (one wave: every entry of A_ik is read before L_ik replaces it)
       T v = T(0);
 #pragma unroll
