@@ -201,12 +201,13 @@ __device__ __forceinline__ void grow_inverse(T* Li, int LS, const T* Lb, T* Y, i
   }
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
-  const int kb = (kp + 15) / 16;  // column blocks of the finished part (at most 3)
+  const int kb = (kp + 15) / 16;  // column blocks of the finished part (at most 4)
   for (int b = wv; b < kb; b += nw) {
     typename MF::acc_t acc = MF::zero();
-    for (int m = 0; m < 16 * kb; m += 4) {
-      // (rows >= kp of Li are still zero)
-      const T av = (li < sw && m + lg < kp) ? Lb[li * 64 + m + lg] : T(0);
+    // (kp is a multiple of 4; rows kp .. are written below by another wave
+    // before the barrier, so none of them may be read here)
+    for (int m = 0; m < kp; m += 4) {
+      const T av = li < sw ? Lb[li * 64 + m + lg] : T(0);
       acc = MF::mac(av, Li[(m + lg) * LS + 16 * b + li], acc);
     }
 #pragma unroll
