@@ -48,7 +48,12 @@ template <typename T>
 hipError_t condense_panel(const CondenseWork<T>& w, int lw, int c0, int cb, int ce, int right, hipStream_t s);
 
 // Untuned sub-panel width for elements of n local dofs and t trace dofs: 16,
-// but 8 for FP64 elements with more than 512 rows of A or of C.
+// but 8 for FP64 elements with more than 512 rows of A or of C and for FP32
+// ones with more than 1536 or 512.  512 elements, 8 against 16 wide: FP64
+// n = 160 0.67 / 0.66 ms, n = 540 7.9 / 7.8, n = 1280 50.0 / 49.8, and n = 2500,
+// where a thread's rows of 16 FP64 columns are spilled, 301 / 326; FP32 n = 540
+// 5.5 / 4.9, n = 1280 29.7 / 25.6, and n = 2500 162 / 141, where the tuned table
+// takes 16.
 inline int default_leaf_width(size_t elem_bytes, int n, int t) {
   const int qa = (n + 511) / 512, qc = (t + 511) / 512;
   const int q = (qa <= 1 && qc <= 1) ? 2 : (qa <= 3 && qc <= 1) ? 4 : 7;
@@ -57,7 +62,10 @@ inline int default_leaf_width(size_t elem_bytes, int n, int t) {
 
 // Untuned panel width: 128 columns for FP32 storage (FP32 or BF16
 // operands) and elements of at least 1024 local dofs, else 64 (the only
-// width FP64 storage is built for).
+// width FP64 storage is built for).  A wider panel halves the launches and
+// reads of L and costs the update between its halves: 512 elements, 64 against
+// 128 wide, FP32 n = 540 4.9 / 5.5 ms, n = 1280 25.6 / 25.6, n = 2500 148 / 141;
+// BF16 4.1 / 4.3, 20.0 / 18.4, 114 / 92.
 inline int default_panel_width(size_t elem_bytes, int n) {
   return elem_bytes == 4 && n >= 1024 ? 128 : 64;
 }

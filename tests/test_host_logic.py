@@ -141,3 +141,19 @@ def test_batch_group_branches(monkeypatch):
     one = next(x for x in br if a in x)
     for p, q in ((a, c), (b, d), (a, e), (d, e)):
         assert one.index(p) < one.index(q)
+
+
+def test_autotuner_keeps_a_choice_within_its_margin():
+    from paper_1605_01020_amd import autotune
+    t = {(8, 64): 1.0, (16, 64): 1.015, (8, 128): 1.03}
+    assert autotune.choose(t) == (8, 64)
+    assert autotune.choose(t, (16, 64)) == (16, 64)      # within 2% of the fastest
+    assert autotune.choose(t, (8, 128)) == (8, 64)       # not
+    assert autotune.choose(t, (16, 128)) == (8, 64)      # not built
+    # every stored choice is the fastest of its row or within the margin
+    import json
+    with open(autotune.TUNING_PATH) as f:
+        for e in json.load(f)["entries"]:
+            ms = {tuple(map(int, k.split("/"))): v for k, v in e["ms"].items()}
+            kept = (e["leaf_width"], e["panel_width"])
+            assert autotune.choose(ms, kept) == kept, e
