@@ -30,7 +30,6 @@ struct CondenseWork {
   int n, t;
   // the panels' inverses do not fit the elements' Ke blocks (small t)
   int self;
-  int spread;  // consecutive tiles of an element on consecutive XCDs
 };
 
 // Condenses every item of w: sub-panel width lw (8 or 16), panel width ct
@@ -131,25 +130,21 @@ __device__ __forceinline__ Elem<T> condense_elem(const CondenseWork<T>& wk, int 
 }
 
 // Tile kernels: block -> (item, tile).  Workgroups go to the 8 XCDs in turn
-// by block index, so with the spread off every tile of an item (and the next
-// launch's tiles of it) runs on one XCD and shares operands in its L2.  Few
-// items would leave XCDs idle that way: those spread an item's tiles.
+// by block index, so that every tile of an item (and the next launch's tiles of
+// it) runs on one XCD and shares operands in its L2.  Consecutive tiles on
+// consecutive XCDs measured no better for few items either, down to one: 1, 8,
+// 64 FP64 elements of n = 540 1.737, 1.737, 2.152 ms against 1.750, 1.752,
+// 2.172, BF16 of n = 2500 10.06, 10.60, 17.9 against 10.2, 10.8, 18.9.
 template <typename T>
 __device__ __forceinline__ bool condense_locate(const CondenseWork<T>& wk, int tiles, int& it, int& tile) {
-  const int b = blockIdx.x;
-  if (wk.spread) {
-    it = b / tiles;
-    tile = b % tiles;
-  } else {
-    const int s = b >> 3;
-    it = (s / tiles) * 8 + (b & 7);
-    tile = s % tiles;
-  }
+  const int b = blockIdx.x, s = b >> 3;
+  it = (s / tiles) * 8 + (b & 7);
+  tile = s % tiles;
   return it < wk.count;
 }
 template <typename T>
 inline dim3 condense_grid(const CondenseWork<T>& wk, int tiles) {
-  return dim3((unsigned)((wk.spread ? wk.count : (wk.count + 7) / 8 * 8) * tiles));
+  return dim3((unsigned)((wk.count + 7) / 8 * 8 * tiles));
 }
 
 // ---- growing L_pp^{-1} where L may hold infinities or NaN -----------------------

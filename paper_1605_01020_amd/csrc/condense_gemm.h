@@ -19,7 +19,7 @@
 //   for each panel [c0, c1):
 //     1. condense_col:   M[c0:, c0:c1] = in - L[c0:, :c0] U[:c0, c0:c1]
 //     2. condense_panel: the panel is factored (a 128-wide one as two halves
-//        of 64 with condense_half, one update, between them); its L^{-1} goes
+//        of 64 with condense_col's HALF form, one update, between them); its L^{-1} goes
 //        to scratch
 //     3. condense_row:   U[c0:c1, c1:] = L_pp^{-1} (in - L[c0:c1, :c0] U[:c0, c1:])
 //   4. condense_schur: M[n:, n:] = in - L21 U12
@@ -649,7 +649,6 @@ template <typename T, int MM>
 hipError_t condense_run(const CondenseWork<T>& w0, int lw, int ct, hipStream_t s) {
   CondenseWork<T> w = w0;
   w.self = !inverse_fits(w.n, w.t, ct);
-  w.spread = w.count < 64;
   if (w.count == 0) return hipSuccess;
   if constexpr (sizeof(T) == 4) {
     if (ct == 128) return condense_sequence<T, MM, 128>(w, lw, s);
