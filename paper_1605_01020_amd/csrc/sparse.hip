@@ -104,8 +104,13 @@ __global__ void assemble_r_kernel(int n_face, int b, int t, int S, const int32_t
 //   units on more threads make it one or two rounds: 40 rows of b = 45 a level
 //   took 8.3 us in the other form and take 6.0; where the GPU is full the units
 //   cost more than they save (FP32, 6,656 rows: 336 -> 455 us).
+// kManyRows: two workgroups a CU, where the two forms cross: sweeps of 320, 500
+// and 720 rows a level, CS = 0 against 16, whole application: b = 45 FP64 136 /
+// 104, 168 / 157, 208 / 213 us, b = 80 FP32 221 / 186, 242 / 250, 281 / 354;
+// SpMV of 240 and 756 rows b = 45 FP64 14.4 / 10.6, 24.8 / 25.5, b = 80 FP32
+// 20.2 / 18.0, 29.9 / 47.1.
 constexpr int PTHR = 512;
-constexpr int kManyRows = 512;  // two workgroups a CU
+constexpr int kManyRows = 512;
 template <typename T, int CS>
 __device__ inline double block_row_sum(int b, const T* blocks, const int32_t* col_face, int s0, int s1,
                                        const double* x, int g, int G, int rr) {
