@@ -19,8 +19,8 @@
 //   for each panel [c0, c1):
 //     1. condense_col:   M[c0:, c0:c1] = in - L[c0:, :c0] U[:c0, c0:c1]
 //     2. condense_panel: the panel is factored (a 128-wide one as two halves
-//        of 64 with condense_col's HALF form, one update, between them); its L^{-1} goes
-//        to scratch
+//        of 64 with one update, condense_col with HALF = 1, between them); its
+//        L^{-1} goes to scratch
 //     3. condense_row:   U[c0:c1, c1:] = L_pp^{-1} (in - L[c0:c1, :c0] U[:c0, c1:])
 //   4. condense_schur: M[n:, n:] = in - L21 U12
 // One workgroup per element for the whole elimination would leave the chip
@@ -63,7 +63,10 @@ typedef short bf16x4 __attribute__((ext_vector_type(4)));
 //
 // What bounds it: the matrix cores (FP32: 105 TFLOP/s of 155 where K is long,
 // 112 in the Schur block), and for short K the inputs, read in 1 KB pieces of
-// rows at 3 TB/s.  L is read a row at a time with rows far apart, so a slab is as deep as a
+// rows at 3 TB/s (the first panel's columns, which have no product).  BF16
+// (216 elements of n = 2500): the operands' reads from beyond the L2, 3.7 TB/s
+// for the whole of the panel columns, vector instructions issuing 31% of the
+// time and the matrix cores busy 12%.  L is read a row at a time with rows far apart, so a slab is as deep as a
 // cache line is long, 32 in FP32 (16 deep, two slabs in LDS, left waves
 // waiting 58% of the time and the matrix cores busy 48%) and 16 in FP64 (32
 // deep costs a wave a SIMD: 512 elements of n = 1280 54.2 ms, 49.5 ms 16 deep).
