@@ -394,22 +394,22 @@ void condense_panel_kernel(CondenseWork<T> wk, int c0, int cb, int ce, int right
           const T bv = li < LW && m + lg < kp ? sm.Xu[(m + lg) * LW + (li & (LW - 1))] : T(0);
           acc = MF::mac(sm.Li[(16 * ib + li) * LIS + m + lg], bv, acc);
         }
+        if (li < LW) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sm.Ut[(16 * ib + MF::row(lane, v)) * LW + row_slot<LW>(li)] = acc[v];
+        }
         if (__builtin_expect(any_nonfinite(acc), 0)) {  // (the zeros above the diagonal met an infinity)
           int ln = lane;
           asm volatile("" : "+v"(ln));  // (cold: nothing of it is computed ahead and kept)
+          const int j = ln & 15;
 #pragma unroll 1
           for (int v = 0; v < 4; ++v) {
             const int i = 16 * ib + MF::row(ln, v);
             T s = T(0);
 #pragma unroll 1
-            for (int m = 0; m <= min(i, kp - 1); ++m) s = fma(sm.Li[i * LIS + m], sm.Xu[m * LW + (ln & (LW - 1))], s);
-            acc[0] = v == 0 ? s : acc[0]; acc[1] = v == 1 ? s : acc[1];
-            acc[2] = v == 2 ? s : acc[2]; acc[3] = v == 3 ? s : acc[3];
+            for (int m = 0; m <= min(i, kp - 1); ++m) s = fma(sm.Li[i * LIS + m], sm.Xu[m * LW + (j & (LW - 1))], s);
+            if (j < LW) sm.Ut[i * LW + (j & 3) * (LW / 4) + (j >> 2)] = s;
           }
-        }
-        if (li < LW) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) sm.Ut[(16 * ib + MF::row(lane, v)) * LW + row_slot<LW>(li)] = acc[v];
         }
       }
       __syncthreads();
